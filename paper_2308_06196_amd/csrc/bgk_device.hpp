@@ -23,7 +23,7 @@
 // chunk of 256 consecutive velocity slots; one lane = one velocity slot j and all
 // (p+1)^d nodes of the element, held in registers (quadrilaterals, and
 // hexahedra in FP32; the plane-split hexahedral kernels are in
-// bgk_device3d.hpp). The FR operators are
+// bgk_hexwalk.hpp and bgk_device3d.hpp). The FR operators are
 // (p+1)-point contractions along element lines (sum factorisation, VALU);
 // they are far below the FP64/FP32 ridge point, so the kernel is bound by
 // HBM traffic and instruction issue, not by arithmetic peak.
@@ -144,6 +144,9 @@ struct StageArgs {
   int32_t rc_mask;
   int32_t sweep_seg;  // column sweeps: elements per work item along the last axis
   int32_t xcd_part;   // XCDs per chunk group of xcd_chunk_remap (else xcd_remap)
+  // hexahedral walk (k_stage_walk): elements per tile row, rows per tile, most
+  // row entries per node of any velocity chunk
+  int32_t walk_tx, walk_ty, walk_ncols;
 };
 
 // BF16 <-> FP32: the upper half of the FP32 bit pattern; rounding to nearest,
@@ -350,19 +353,9 @@ __host__ __device__ __forceinline__ void slot_nodes(const DevGeom& g, int j, int
   for (int k = 0; k < 3; ++k) b[k] = l[k] + ((o >> k) & 1 ? g.vsplit[k] : 0);
 }
 
-// LEX: the grid has a single octant (slots are the lexicographic indices),
-// decoded with the grid's own, uniform divisors.
-template <bool LEX = false>
 __device__ __forceinline__ Vel velocity_of(const DevGeom& g, int j) {
   Vel v;
-  if constexpr (LEX) {
-    const int r = j / g.nv1[0];
-    v.b[0] = j - r * g.nv1[0];
-    v.b[2] = r / g.nv1[1];
-    v.b[1] = r - v.b[2] * g.nv1[1];
-  } else {
-    slot_nodes(g, j, v.b);
-  }
+  slot_nodes(g, j, v.b);
   double w = 1.0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -660,9 +653,13 @@ __device__ __forceinline__ void element_partials_mfma(const CT (&fv)[NS], const 
 // its discrete moments vanish to FP64 rounding (the conservation the Newton
 // solve of the equilibrium reaches); bgk_collision_moments measures them with
 // the same function.
+__device__ __forceinline__ double collision_term(double ex, double ey, double ez, double itau,
+                                                 double f) {
+  return fma(-f, itau, ex * ey * ez);
+}
 __device__ __forceinline__ double collision_term(const double* ti, int bx, int oy, int oz, int S,
                                                  double f) {
-  return fma(-f, ti[S - 1], ti[bx] * ti[oy] * ti[oz]);
+  return collision_term(ti[bx], ti[oy], ti[oz], ti[S - 1], f);
 }
 
 // Stored BF16 increment of a stage value o over the FP32 base F, and the
@@ -681,7 +678,24 @@ __device__ __forceinline__ uint16_t bf16_increment(float o, float base, float& s
   stored = base + bf16_f32(h);
   return h;
 }
-
+// Two stage values of successive nodes as one word of the increment buffer
+// (bf16_increment of each; the first in the low half), and the values that the
+// next stage reads. v_cvt_pk_bf16_f32 rounds both to nearest even, v_perm takes
+// the truncated halves and the sign masks that choose between them.
+__device__ __forceinline__ uint32_t bf16_increment2(float o0, float o1, float base0, float base1,
+                                                    float& stored0, float& stored1) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  const f2 d = {o0 - base0, o1 - base1};
+  const uint32_t near = __builtin_bit_cast(uint32_t, __builtin_convertvector(d, b2));
+  const uint32_t u0 = __float_as_uint(d.x), u1 = __float_as_uint(d.y);
+  const uint32_t trunc = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+  const uint32_t neg = __builtin_amdgcn_perm(u1, u0, 0x0B0B0909u);
+  const uint32_t h = (trunc & neg) | (near & ~neg);
+  stored0 = base0 + bf16_lo(h);
+  stored1 = base1 + bf16_hi(h);
+  return h;
+}
 
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
 
@@ -1280,21 +1294,31 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
         const int64_t ooff = f_offset(g, e, 0, jj);
         uint32_t* ow = inc_pairs((uint16_t*)A.out, ooff);
         float omin = INFINITY, smin = INFINITY;  // stage values / stored values
-        uint32_t hp = 0;
+        uint32_t wd[NS / 2];
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-          float stored;
-          const uint16_t h = bf16_increment(o[i], fnv[i], stored);
-          if (i % 2 == 0 && i == NS - 1) {
+        for (int i = 0; i < NS; i += 2) {
+          if (i == NS - 1) {  // odd last node
+            float stored;
+            const uint16_t h = bf16_increment(o[i], fnv[i], stored);
             if (valid) __builtin_nontemporal_store(h, (uint16_t*)A.out + ooff + i * kVB);
-          } else if (i % 2 == 0) {
-            hp = h;
-          } else if (valid) {
-            __builtin_nontemporal_store(hp | ((uint32_t)h << 16), &ow[(i >> 1) * kVB]);
+            omin = fminf(omin, o[i]);
+            smin = fminf(smin, stored);
+            o[i] = stored;
+          } else {
+            constexpr int kLast = NS - 1;
+            const int k = i < kLast ? i + 1 : i;
+            float s0, s1;
+            const uint32_t w = bf16_increment2(o[i], o[k], fnv[i], fnv[k], s0, s1);
+            wd[i >> 1] = w;
+            omin = fminf(omin, fminf(o[i], o[k]));
+            smin = fminf(smin, fminf(s0, s1));
+            o[i] = s0;
+            o[k] = s1;
           }
-          omin = fminf(omin, o[i]);
-          smin = fminf(smin, stored);
-          o[i] = stored;
+        }
+        if (valid) {
+#pragma unroll
+          for (int m = 0; m < NS / 2; ++m) __builtin_nontemporal_store(wd[m], &ow[m * kVB]);
         }
         // slices whose stored stage is negative where the stage itself is not
         const unsigned long long nviol = __popcll(__ballot(valid && smin < 0.0f && !(omin < 0.0f)));

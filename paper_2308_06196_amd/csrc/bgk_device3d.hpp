@@ -1,10 +1,10 @@
-// bgk_device3d.hpp -- stage and moment kernels for hexahedral (d = 3)
-// elements on gfx950 (Dzanic & Martinelli, arXiv 2308.06196, Sec. 2.1).
+// bgk_device3d.hpp -- residual and moment kernels of hexahedral (d = 3)
+// elements that do not fit one lane's registers, on gfx950 (Dzanic &
+// Martinelli, arXiv 2308.06196, Sec. 2.1).
 //
-// Plane-split kernels, used where a (p+1)^3-node element does not fit one
-// lane's registers: FP64 storage, and the BF16-increment stages (which hold a
-// second value per neighbour node). FP32 hexahedra run the one-lane-per-
-// velocity k_stage<3, ...> of bgk_device.hpp instead. Here a group of G lanes
+// Used at p = 3 with FP64 storage and BF16 increments (the RK stages of these
+// solvers are k_stage_walk's, bgk_hexwalk.hpp); the other hexahedra run the
+// one-lane-per-velocity kernels of bgk_device.hpp. Here a group of G lanes
 // (G = 2 for p = 1, 4 for p = 2, 3) shares one velocity and lane g of the
 // group owns the z-plane a_z = g of the element: (p+1)^2 nodes. The x and
 // y operators are lane-local exactly as for quadrilaterals; the z-derivative
@@ -26,22 +26,12 @@ template <int P> struct Plane3 {
   static constexpr int NS = N1 * N1 * N1;
 };
 
-// Sum / min over the G lanes of a group (partners lane ^ 1, lane ^ 2; every
-// lane ends with the same bits).
+// Sum over the G lanes of a group (partners lane ^ 1, lane ^ 2; every lane ends
+// with the same bits).
 template <int G, typename T>
 __device__ __forceinline__ T group_allsum(T x) {
   x += quad_xor<1>(x);
   if constexpr (G == 4) x += quad_xor<2>(x);
-  return x;
-}
-template <int G, typename T>
-__device__ __forceinline__ T group_allmin(T x) {
-  T y = quad_xor<1>(x);
-  x = y < x ? y : x;
-  if constexpr (G == 4) {
-    y = quad_xor<2>(x);
-    x = y < x ? y : x;
-  }
   return x;
 }
 
@@ -101,39 +91,21 @@ __device__ __forceinline__ void plane_partials_mfma(const CT (&fv)[Plane3<P>::P2
 }
 
 
-// One work item (element e x velocity chunk) of the plane-split stage. With
-// SW (column sweep along z, see stage_item) the group's z-outflow traces are
-// carried from the previous element of the column in LDS (one value per
-// velocity and z-line, written by the group's first lane).
-// The (p+1)^2 values of one plane of a neighbour (BF16-increment stages:
-// F + increment).
-template <int P2, bool DIN, typename CT, typename ST>
-__device__ __forceinline__ void load_planes(CT (&v)[P2], const ST* src, const ST* fin,
-                                            const uint16_t* din) {
-#pragma unroll
-  for (int q = 0; q < P2; ++q) v[q] = (CT)src[q * kVB];
-  if constexpr (DIN) add_increments(v, din, src - fin);
-}
-
-template <int P, typename ST, int MODE, bool INC = false, bool SW = false>
-__device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk, const int64_t e,
-                                            const bool count, const bool carry, const bool up) {
-  static_assert(!INC || (MODE != 1 && sizeof(ST) == 4), "increment stages: FP32 state, RK modes");
-  static_assert(!SW || MODE != 1, "column sweeps: RK modes");
+// One work item (element e x velocity chunk) of the residual L(f) in FP64 (the
+// RK stages of these elements are k_stage_walk's, bgk_hexwalk.hpp).
+template <int P, typename ST>
+__device__ __forceinline__ void residual3_item(const StageArgs& A, const int chunk, const int64_t e,
+                                               const bool count) {
   using CT = typename Compute<ST>::T;
   using PL = Plane3<P>;
   constexpr bool kMfma = sizeof(CT) == 4;
   constexpr int N1 = PL::N1, G = PL::G, VB = PL::VB, P2 = PL::P2, NS = PL::NS;
-  __shared__ double red[(kBlock / 64) * NS * 5];
   __shared__ FaceRows<CT> frows[kBlock / 64];
   __shared__ LineOps lops[kMfma ? kBlock / 64 : 1];
-  __shared__ CT trl[SW ? P2 * VB : 1];  // carried z-traces, [line][velocity of the work-group]
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   double* tab = reinterpret_cast<double*>(dyn_lds);
 
-  // thread index, opaque per element in a sweep (see stage_item)
-  int tid = (int)threadIdx.x;
-  if constexpr (SW) asm volatile("" : "+v"(tid));
+  const int tid = (int)threadIdx.x;
   const DevGeom& g = A.g;
   const DevOpsT<CT>& OP = ops_of<CT>(A);
   FaceRows<CT>& fr = frows[tid >> 6];
@@ -148,11 +120,9 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
   const bool live = lp < N1;
   const int pl = live ? lp : N1 - 1;             // address plane (idle lanes)
   const int j = chunk * VB + tid / G;
-  const bool valid = j < nv;
-  const bool act = valid && live;
-  const int jj = valid ? j : (int)nv - 1;
-  Vel vel = velocity_of<sizeof(ST) == 8>(g, jj);  // FP64: lexicographic slots
-  if (!act) vel.w = 0.0;
+  const bool act = j < nv && live;
+  const int jj = j < nv ? j : (int)nv - 1;
+  const Vel vel = velocity_of(g, jj);
 
   int ek[3];
   {
@@ -193,23 +163,10 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
     use_right[k] = (pos[k] != wall);
     src[k] = fin + f_offset(g, src_e, pl * P2, src_j);
   }
-  // sweep: groups whose upwind z-neighbour is the previous element of the
-  // column take its carried traces; a wave loads the z-neighbour's planes only
-  // when one of its groups does not (uniform)
-  bool lane_carry = false, wave_load = true;
-  if constexpr (SW) {
-    lane_carry = carry && pos[2] == up;
-    // every wave loads at the column's entry element, also one whose lanes
-    // are all beyond the velocity count: their carried values must be finite
-    // (they enter the moment partials with weight 0)
-    wave_load = !carry || __ballot(valid && !lane_carry) != 0;
-  }
 
-  // loads: equilibrium rows (first batch), own plane, the x-, y- and
-  // z-neighbours' planes, f^n plane
   // first batch of row loads: 4 x 256 entries for FP32 arithmetic, whose
   // registers are scarcer, 6 x 256 in FP64 (a 64-velocity chunk of the 16^3
-  // grid at p = 3 needs 64 x 22)
+  // grid at p = 3 needs 64 x 18 or more)
   constexpr int kU = kMfma ? 4 : 6;
   const RowPick rp = row_pick(A, chunk, NS);
   const double* et = A.etab + node0 * S;
@@ -221,37 +178,12 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
       tv[u] = et[rp.offset(t < rp.count ? t : rp.count - 1)];
     }
   }
-  // BF16-increment stages 2-3: the input is F + increment (same offsets)
-  constexpr bool kDin = INC && MODE == 0;
-  const uint16_t* __restrict__ din = A.din;
   const ST* fe = fin + f_offset(g, e, pl * P2, jj);
-  CT f[P2];
+  CT f[P2], nb[P2];
 #pragma unroll
   for (int q = 0; q < P2; ++q) f[q] = (CT)fe[q * kVB];
-  // sweep: the z-neighbour's planes are not held (see the z part). The
-  // neighbours' planes are loaded one axis at a time (the next axis' after
-  // this axis' transport), so that no more than one neighbour's planes are
-  // held at once: FP64 fits three waves per SIMD (167 registers against 234
-  // with all loaded up front), BF16 increments four (128 against 157).
-  constexpr int NB = SW ? 2 : 3;
-  constexpr bool kStaged = true;
-  CT nb[NB][P2];
-  if constexpr (kStaged) {
-    load_planes<P2, kDin>(nb[0], src[0], fin, din);
-  } else {
 #pragma unroll
-    for (int k = 0; k < NB; ++k)
-#pragma unroll
-      for (int q = 0; q < P2; ++q) nb[k][q] = (CT)src[k][q * kVB];
-  }
-  if constexpr (kDin) {
-    add_increments(f, din, fe - fin);
-    if constexpr (!kStaged) {
-#pragma unroll
-      for (int k = 0; k < NB; ++k) add_increments(nb[k], din, src[k] - fin);
-    }
-  }
-
+  for (int q = 0; q < P2; ++q) nb[q] = (CT)src[0][q * kVB];
   if (A.collide) {
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
@@ -266,12 +198,14 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
 
   // x and y: lines inside the plane, lane-local (FP32 arithmetic on the matrix
   // cores, see line_mfma: a block of four lanes is one velocity's planes for
-  // p >= 2, two velocities for p = 1)
+  // p >= 2, two velocities for p = 1). The neighbours' planes are loaded one
+  // axis at a time, behind a scheduling barrier.
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    if (kStaged && k > 0) {  // keep the scheduler from hoisting these loads
+    if (k > 0) {
       __builtin_amdgcn_sched_barrier(0);
-      load_planes<P2, kDin>(nb[k], src[k], fin, din);
+#pragma unroll
+      for (int q = 0; q < P2; ++q) nb[q] = (CT)src[k][q * kVB];
     }
     const int S1 = k == 0 ? 1 : N1;
     const CT a = (CT)(vel.u[k] * g.scale[k]);
@@ -291,7 +225,7 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
 #pragma unroll
           for (int bb = 0; bb < N1; ++bb) {
             fl[bb] = f[base + bb * S1];
-            nl[bb] = nb[k][base + bb * S1];
+            nl[bb] = nb[base + bb * S1];
           }
           const mfma_f4 c = line_mfma<N1>(dp, ev, fl, nl);
 #pragma unroll
@@ -321,7 +255,7 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
 #pragma unroll
       for (int bb = 0; bb < N1; ++bb) {
         own += lown[bb] * line[bb];
-        ext += lext[bb] * nb[k][base + bb * S1];
+        ext += lext[bb] * nb[base + bb * S1];
       }
       const CT jump = a * (ext - own);
 #pragma unroll
@@ -333,10 +267,9 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
       }
     }
   }
-  if constexpr (kStaged && !SW) {
-    __builtin_amdgcn_sched_barrier(0);
-    load_planes<P2, kDin>(nb[NB - 1], src[2], fin, din);
-  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < P2; ++q) nb[q] = (CT)src[2][q * kVB];
   // z: the column of node q is spread over the group's lanes; lane lp holds
   // plane lp and its partners lane ^ r the other planes. The derivative is
   // sum_r D[lp][lp ^ r] f(lp ^ r); the trace difference ext - own is one
@@ -347,23 +280,7 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
     const CT* re = fr.r[use_right[2] ? 0 : 1];
     const CT lown_mine = live ? ro[pl] : (CT)0;
     const CT lext_mine = live ? re[pl] : (CT)0;
-    const CT lout_mine = live ? fr.r[up ? 0 : 1][pl] : (CT)0;  // sweep: outflow trace weight
-    const int vg = tid / G;                                 // velocity inside the work-group
     const CT ag = a * ro[kMaxN1 + pl];
-    // sweep: every group takes its z-exterior traces from trl; where a wave
-    // has groups that do not carry, those groups first put there the traces
-    // formed from the z-neighbour's planes
-    if constexpr (SW) {
-      if (wave_load) {
-#pragma unroll
-        for (int q = 0; q < P2; ++q) {
-          CT v = (CT)src[2][q * kVB];
-          if constexpr (kDin) v += increment_of<P2>(din, src[2] - fin, q);
-          const CT t = group_allsum<G>(lext_mine * v);
-          if (!lane_carry) trl[q * VB + vg] = t;
-        }
-      }
-    }
     CT Dr[G];
 #pragma unroll
     for (int r = 0; r < G; ++r) {
@@ -379,192 +296,41 @@ __device__ __forceinline__ void stage3_item(const StageArgs& A, const int chunk,
         df += Dr[2] * quad_xor<2>(fq);
         df += Dr[3] * quad_xor<3>(fq);
       }
-      CT jl;
-      if constexpr (SW) {
-        jl = trl[q * VB + vg] - group_allsum<G>(lown_mine * fq);
-        // outflow trace of this line for the next element of the column
-        // (every lane of the group writes the same value)
-        trl[q * VB + vg] = group_allsum<G>(lout_mine * fq);
-      } else {
-        jl = group_allsum<G>(lext_mine * nb[NB - 1][q] - lown_mine * fq);
-      }
+      const CT jl = group_allsum<G>(lext_mine * nb[q] - lown_mine * fq);
       acc[q] += a * df + ag * jl;
     }
   }
 
-  // relaxation folded with the transport into h = b (f - dt T) + b dt C
-  // before f^n is loaded (as in stage_item: C in FP64 from the FP64 rows,
-  // added in FP64), all inside the branch that loads the rows
-  // positions of this velocity's factors in a node's LDS row (compact)
+  // collision term in FP64 from the rows in LDS; the residual C - T goes to
+  // the canonical layout
   const int cx = vel.b[0] - rp.x0, oy = rp.nx + vel.b[1] - rp.y0,
             oz = rp.nxy + vel.b[2] - rp.z0;
   const double* tp = tab + pl * P2 * rp.ncols;  // rows of this lane's plane
-  double* oe1 = nullptr;                 // residual output (MODE 1)
-  if constexpr (MODE == 1) {
-    const int jc = vel.b[0] + g.nv1[0] * (vel.b[1] + g.nv1[1] * vel.b[2]);
-    oe1 = (double*)A.out + ((e - A.out_e0) * NS + pl * P2) * nv + jc;
-  }
-  const CT dt = (CT)A.dt, ca = (CT)A.a, cb = (CT)A.b;
-  const double wc = A.b * A.dt;
+  const int jc = vel.b[0] + g.nv1[0] * (vel.b[1] + g.nv1[1] * vel.b[2]);
+  double* oe1 = (double*)A.out + ((e - A.out_e0) * NS + pl * P2) * nv + jc;
   if (A.collide) {  // uniform: rows beyond the first batch, then the relaxation
     table_rest<kU>(tab, et, rp, tid);
     lds_barrier();
 #pragma unroll
     for (int q = 0; q < P2; ++q) {
       const double c = collision_term(tp + q * rp.ncols, cx, oy, oz, rp.ncols, (double)f[q]);
-      if constexpr (MODE == 1) {
-        if (act) oe1[(int64_t)q * nv] = c - (double)acc[q];
-      } else if constexpr (sizeof(CT) == 8) {  // h, kept in acc
-        acc[q] = fma(wc, c, cb * (f[q] - dt * acc[q]));
-      } else {
-        acc[q] = (CT)fma(wc, c, (double)(cb * (f[q] - dt * acc[q])));
-      }
+      if (act) oe1[(int64_t)q * nv] = c - (double)acc[q];
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < P2; ++q) {
-      if constexpr (MODE == 1) {
-        if (act) oe1[(int64_t)q * nv] = -(double)acc[q];
-      } else {
-        acc[q] = cb * (f[q] - dt * acc[q]);
-      }
-    }
+    for (int q = 0; q < P2; ++q)
+      if (act) oe1[(int64_t)q * nv] = -(double)acc[q];
   }
-  // f^n (MODE 0; a stream, see stage_item), or F of the own nodes, the base
-  // of the BF16 increments (read again: a cache hit)
-  CT fnv[P2];
-  // keep the scheduler from hoisting these loads above the relaxation
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (INC) {
-#pragma unroll
-    for (int q = 0; q < P2; ++q) fnv[q] = (CT)fe[q * kVB];
-  } else if constexpr (MODE == 0) {
-    const ST* fn = (const ST*)A.fn + f_offset(g, e, pl * P2, jj);
-#pragma unroll
-    for (int q = 0; q < P2; ++q) fnv[q] = (CT)__builtin_nontemporal_load(&fn[q * kVB]);
-  }
-  CT o[P2];
-  if constexpr (MODE != 1) {
-#pragma unroll
-    for (int q = 0; q < P2; ++q) o[q] = MODE == 0 ? ca * fnv[q] + acc[q] : acc[q];
-  }
-
-  if constexpr (MODE == 1) {
-    if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
-  } else {
-    if (A.limiter) {
-      // element mean and minimum over all planes of the velocity
-      CT wz = (CT)0;  // Gauss weight of this lane's plane
-#pragma unroll
-      for (int bb = 0; bb < N1; ++bb) wz = bb == lp ? sreg(OP.w[bb]) : wz;
-      CT part = wz * tensor_wsum<2, N1>(o, OP.w);
-      CT fmin = o[0];
-#pragma unroll
-      for (int q = 0; q < P2; ++q) fmin = o[q] < fmin ? o[q] : fmin;
-      if (!live) {
-        part = (CT)0;
-        fmin = (CT)INFINITY;
-      }
-      const CT mean = group_allsum<G>(part) / OP.Wsum;
-      fmin = group_allmin<G>(fmin);
-      const bool hit = valid && (fmin < (CT)0);
-      if (hit && mean != fmin) {
-        CT beta = fabs(mean / (mean - fmin));
-        beta = beta > (CT)1 ? (CT)1 : beta;
-#pragma unroll
-        for (int q = 0; q < P2; ++q) o[q] = mean + beta * (o[q] - mean);
-      }
-      const unsigned long long nh = __popcll(__ballot(hit && lp == 0));
-      const unsigned long long nb2 = __popcll(__ballot(hit && lp == 0 && !(mean > (CT)0)));
-      if ((tid & 63) == 0 && nh) {
-        atomicAdd(&A.diag[2], nh);
-        if (nb2) atomicAdd(&A.diag[3], nb2);
-      }
-    }
-    if constexpr (INC) {
-      // the increment o - F in BF16, and the stored state F + increment for
-      // the partials; the last stage stores o itself in FP32
-      if (A.out_full) {
-        if (act) {
-          ST* oe = (ST*)A.out + f_offset(g, e, pl * P2, j);
-#pragma unroll
-          for (int q = 0; q < P2; ++q) __builtin_nontemporal_store((ST)o[q], &oe[q * kVB]);
-        }
-      } else {
-        static_assert(P2 % 2 == 0, "BF16 planes hold whole node pairs");
-        uint32_t* ow = inc_pairs((uint16_t*)A.out, f_offset(g, e, pl * P2, jj));
-        float omin = INFINITY, smin = INFINITY;  // stage values / stored values
-        uint32_t hp = 0;
-#pragma unroll
-        for (int q = 0; q < P2; ++q) {
-          float stored;
-          const uint16_t h = bf16_increment(o[q], fnv[q], stored);
-          if (q % 2 == 0) {
-            hp = h;
-          } else if (act) {
-            __builtin_nontemporal_store(hp | ((uint32_t)h << 16), &ow[(q >> 1) * kVB]);
-          }
-          omin = fminf(omin, o[q]);
-          smin = fminf(smin, stored);
-          o[q] = stored;
-        }
-        // (velocity, plane) pairs whose stored stage is negative where the
-        // stage itself is not
-        const unsigned long long nviol = __popcll(__ballot(act && smin < 0.0f && !(omin < 0.0f)));
-        if ((tid & 63) == 0 && nviol) atomicAdd(&A.diag[5], nviol);
-      }
-    } else if (act) {
-      ST* oe = (ST*)A.out + f_offset(g, e, pl * P2, j);
-#pragma unroll
-      for (int q = 0; q < P2; ++q) __builtin_nontemporal_store((ST)o[q], &oe[q * kVB]);
-    }
-    // moment partials on the matrix cores; the staging area reuses the
-    // equilibrium rows' LDS once every wave is done with them
-    if (A.collide) lds_barrier();
-    plane_partials_mfma<P, ST, CT>(o, vel, A.partials, node0, g.nx, chunk, lp, dyn_lds, red, tid);
-    if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
-  }
+  if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
 }
 
-// Waves per SIMD of the plane-split kernels: three in FP64, four in FP32
-// arithmetic (the neighbours' planes loaded one axis at a time); the FP64
-// sweep keeps two (its loop spills at three).
-template <typename CT, bool SW>
-constexpr int plane_waves() {
-  return sizeof(CT) == 8 ? (SW ? 2 : 3) : 4;
-}
-
-template <int P, typename ST, int MODE, bool INC = false>
+// Three waves per SIMD in FP64, four in FP32 arithmetic (the neighbours'
+// planes loaded one axis at a time).
+template <int P, typename ST>
 __global__ void __launch_bounds__(kBlock)
-    __attribute__((amdgpu_waves_per_eu(plane_waves<typename Compute<ST>::T, false>())))
-    k_stage3(const StageArgs A) {
+    __attribute__((amdgpu_waves_per_eu(sizeof(ST) == 8 ? 3 : 4))) k_residual3(const StageArgs A) {
   const int64_t w = xcd_chunk_remap(blockIdx.x, gridDim.x, A.ecount, A.xcd_part);
-  stage3_item<P, ST, MODE, INC>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount),
-                                w == 0, false, false);
-}
-
-// Plane-split stage as column sweeps along z (see k_stage_sweep).
-template <int P, typename ST, int MODE, bool INC = false>
-__global__ void __launch_bounds__(kBlock)
-    __attribute__((amdgpu_waves_per_eu(plane_waves<typename Compute<ST>::T, true>())))
-    k_stage3_sweep(const StageArgs A) {
-  const DevGeom& g = A.g;
-  const int nl = sreg(g.nelem[2]), seg = sreg(A.sweep_seg);
-  const int64_t ncol = g.ne / nl, nseg = nl / seg, per_chunk = ncol * nseg;
-  const int64_t w = xcd_chunk_remap(blockIdx.x, gridDim.x, per_chunk, A.xcd_part);
-  const int chunk = (int)(w / per_chunk);
-  const int64_t r = w - (int64_t)chunk * per_chunk;
-  const int64_t sg = r / ncol, col = r - sg * ncol;
-  const bool up = sweep_up(g, chunk * Plane3<P>::VB);
-  // arguments re-read per element (see k_stage_sweep)
-  table_ptr<StageArgs> ap = (table_ptr<StageArgs>)__builtin_amdgcn_kernarg_segment_ptr();
-  for (int s = 0; s < seg; ++s) {
-    const int el = (int)(sg * seg) + s;
-    const int64_t e = col + (int64_t)(up ? el : nl - 1 - el) * ncol;
-    if (s > 0 && !A.collide) lds_barrier();
-    asm volatile("" : "+s"(ap));
-    stage3_item<P, ST, MODE, INC, true>(table_entry(ap, 0), chunk, e, w == 0 && s == 0, s > 0, up);
-  }
+  residual3_item<P, ST>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount), w == 0);
 }
 
 template <int P, typename ST>
@@ -585,7 +351,7 @@ __global__ void __launch_bounds__(kBlock) k_moments3(const StageArgs A) {
   const int j = chunk * VB + (int)threadIdx.x / G;
   const bool valid = j < nv;
   const int jj = valid ? j : (int)nv - 1;
-  Vel vel = velocity_of<sizeof(ST) == 8>(g, jj);  // FP64: lexicographic slots
+  Vel vel = velocity_of(g, jj);
   if (!(valid && live)) vel.w = 0.0;
   const ST* fe = (const ST*)A.fin + f_offset(g, e, pl * P2, jj);
   CT f[P2];

@@ -509,14 +509,15 @@ static inline unsigned grid_of(int64_t n, int b) { return (unsigned)((n + b - 1)
 
 // Hexahedra. The one-lane-per-velocity kernels (k_stage<3, ...>: all
 // (p+1)^3 nodes of a velocity in one lane's registers) run FP32 storage at
-// every order and FP64 storage and BF16 increments at p <= 2; the
-// plane-split kernels (k_stage3: four lanes per velocity, one z-plane each)
-// run FP64 storage and BF16 increments at p = 3, where one lane cannot hold
-// the element (FP64) or the second value per neighbour node (BF16: 137
-// spilled registers). On the 16^3-element Taylor-Green box, ms per stage,
-// plane-split against one-lane: FP64 p = 1 1.18 / 0.82, p = 2 4.95 / 2.50
-// (two waves per SIMD; 6.22 at three, which spill); BF16 p = 1 0.90 / 0.51,
-// p = 2 3.31 / 1.62, p = 3 6.83 / 7.72; FP32 p = 3 5.49 / 3.61.
+// every order and FP64 storage and BF16 increments at p <= 2; the plane-split
+// kernels (four lanes per velocity, one z-plane each: k_stage_walk, k_residual3,
+// k_moments3) run FP64 storage and BF16 increments at p = 3, where one lane
+// cannot hold the element (FP64) or the second value per neighbour node (BF16:
+// 137 spilled registers, 7.72 ms per stage of the 16^3-element Taylor-Green
+// box; k_stage_walk 3.41). At p <= 2 a per-element plane-split stage was slower
+// there (ms, plane-split against one-lane): FP64 p = 1 1.18 / 0.82, p = 2 4.95 /
+// 2.50 (two waves per SIMD; 6.22 at three, which spill); BF16 p = 1 0.90 /
+// 0.51, p = 2 3.31 / 1.62; FP32 p = 3 5.49 / 3.61.
 // The choice (hex_one_lane) is per solver, so that all its kernels share one
 // velocity-chunk width; it must agree with kHexOneLane below.
 template <int P, typename ST>
@@ -525,8 +526,8 @@ constexpr bool kHexOneLane(bool inc) {
 }
 
 // RK stages over the whole mesh run as column sweeps along the last axis
-// (k_stage_sweep, k_stage3_sweep) when the solver chose a segment length and
-// the mesh has no diffuse wall.
+// (k_stage_sweep) when the solver chose a segment length and the mesh has no
+// diffuse wall.
 static bool use_sweep(int mode, const StageArgs& A) {
   if (mode != 0 || A.sweep_seg <= 0 || A.g.dim < 2) return false;
   if (A.e0 != 0 || A.ecount != A.g.ne || A.g.nelem[A.g.dim - 1] % A.sweep_seg != 0) return false;
@@ -558,26 +559,6 @@ static void launch_sweep(bool inc, const StageArgs& A, size_t lds, hipStream_t s
 }
 
 template <int P, typename ST>
-static void launch_sweep3(bool inc, const StageArgs& A, size_t lds, hipStream_t s) {
-  const dim3 grid = sweep_grid(A), block(kBlock);
-  // BF16 increments on planes of whole node pairs (odd p; p = 3 is the one
-  // that runs plane-split, kHexOneLane)
-  if constexpr (sizeof(ST) == 4 && Plane3<P>::P2 % 2 == 0) {
-    if (inc) {
-      if (A.din)
-        hipLaunchKernelGGL((k_stage3_sweep<P, ST, 0, true>), grid, block, lds, s, A);
-      else
-        hipLaunchKernelGGL((k_stage3_sweep<P, ST, 3, true>), grid, block, lds, s, A);
-      return;
-    }
-  }
-  if (A.a != 0.0)
-    hipLaunchKernelGGL((k_stage3_sweep<P, ST, 0>), grid, block, lds, s, A);
-  else
-    hipLaunchKernelGGL((k_stage3_sweep<P, ST, 3>), grid, block, lds, s, A);
-}
-
-template <int P, typename ST>
 static hipError_t hex_dispatch(int mode, bool inc, const StageArgs& A, size_t tab, size_t lds,
                                dim3 grid, dim3 block, hipStream_t s) {
   const bool sweep = use_sweep(mode, A);
@@ -605,28 +586,17 @@ static hipError_t hex_dispatch(int mode, bool inc, const StageArgs& A, size_t ta
       return hipGetLastError();
     }
   }
-  // plane-split; the FP64 ones decode lexicographic slots (one octant)
-  if (sizeof(ST) == 8 && A.g.voct[7] != 0) return hipErrorInvalidValue;
-  const size_t lds3 = mode != 1 ? std::max(tab, (size_t)mfma3_lds_bytes<P, ST>()) : tab;
-  if (sweep) {
-    launch_sweep3<P, ST>(inc, A, lds3, s);
-  } else if (mode == 0 && inc) {
-    if constexpr (sizeof(ST) == 4 && Plane3<P>::P2 % 2 == 0) {
-      if (A.din)
-        hipLaunchKernelGGL((k_stage3<P, ST, 0, true>), grid, block, lds3, s, A);
-      else
-        hipLaunchKernelGGL((k_stage3<P, ST, 3, true>), grid, block, lds3, s, A);
+  if constexpr (P == 3) {  // plane-split: FP64 storage, BF16 increments
+    if (mode == 0) return launch_walk(sizeof(ST) == 8 ? 0 : 2, A, s);
+    if (mode == 1) {
+      hipLaunchKernelGGL((k_residual3<P, ST>), grid, block, tab, s, A);
+    } else {
+      const size_t lds3 = std::max(tab, (size_t)mfma3_lds_bytes<P, ST>());
+      hipLaunchKernelGGL((k_moments3<P, ST>), grid, block, lds3, s, A);
     }
-  } else if (mode == 0 && A.a != 0.0) {
-    hipLaunchKernelGGL((k_stage3<P, ST, 0>), grid, block, lds3, s, A);
-  } else if (mode == 0) {
-    hipLaunchKernelGGL((k_stage3<P, ST, 3>), grid, block, lds3, s, A);
-  } else if (mode == 1) {
-    hipLaunchKernelGGL((k_stage3<P, ST, 1>), grid, block, lds3, s, A);
-  } else {
-    hipLaunchKernelGGL((k_moments3<P, ST>), grid, block, lds3, s, A);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <typename ST>
@@ -688,13 +658,7 @@ static int groups_per_cu(K k, size_t lds) {
 template <int D, int P, typename ST>
 static int sweep_groups_per_cu(bool inc, size_t tab) {
   if constexpr (D == 3) {
-    if (!kHexOneLane<P, ST>(inc)) {
-      const size_t lds = std::max(tab, (size_t)mfma3_lds_bytes<P, ST>());
-      if constexpr (sizeof(ST) == 4 && Plane3<P>::P2 % 2 == 0) {
-        if (inc) return groups_per_cu(k_stage3_sweep<P, ST, 0, true>, lds);
-      }
-      return groups_per_cu(k_stage3_sweep<P, ST, 0>, lds);
-    }
+    if (!kHexOneLane<P, ST>(inc)) return 0;  // k_stage_walk
     if constexpr (sizeof(ST) == 8 && P > 2) return 0;  // not built
   }
   const size_t lds = std::max(tab, (size_t)mfma_lds_bytes<ST>());
@@ -733,10 +697,8 @@ static int sweep_groups(int dim, int order, bool inc, size_t tab) {
 // one lane per velocity: 3.26 / 3.50; the sweep's last axis loads nothing,
 // and without its loads the element fits the registers). Not for FP32 and
 // BF16 quadrilaterals (0.626 / 0.588, the loop costs registers at five waves
-// per SIMD), p = 2 hexahedra (Mach-2 box at four waves per SIMD: spills),
-// FP64 p = 3 hexahedra (the plane-split sweep needs two waves per SIMD where
-// the per-element kernel runs three: 10.2 / 9.88) or BF16 increments at
-// p = 3 (plane-split at four waves per SIMD: 7.36 / 5.84).
+// per SIMD) or p = 2 hexahedra (Mach-2 box at four waves per SIMD: spills).
+// FP64 and BF16 increments at p = 3 walk tiles instead (k_stage_walk).
 static bool sweep_pays(const DevGeom& g, int precision) {
   if (g.dim == 2) return precision == 0;
   return g.dim == 3 && g.n1 == 4 && precision == 1;

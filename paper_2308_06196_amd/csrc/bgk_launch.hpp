@@ -21,6 +21,11 @@ bool hex_one_lane(int order, int precision);
 // Elements per work item of the column-sweep stage kernels for this mesh,
 // velocity grid and storage precision on the current device (0: no sweep).
 int sweep_segment(const DevGeom& g, int precision, bool collide);
+// Plane-split hexahedra (p = 3, FP64 storage or BF16 increments): RK stage by
+// k_stage_walk, and its tile (elements per row, rows); ncols: most row entries
+// per node of any velocity chunk.
+hipError_t launch_walk(int precision, const StageArgs& A, hipStream_t s);
+void walk_tile(const DevGeom& g, int precision, int ncols, int* tx, int* ty);
 // mode 0: fused RK stage (a variant that does not read f^n when a = 0);
 // 1: residual L(f) in FP64; 2: moment partials only.
 hipError_t launch_stage(int precision, int mode, const StageArgs& A, hipStream_t s);

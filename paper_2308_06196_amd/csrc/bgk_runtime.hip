@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "../../include/bgk.h"
+#include "bgk_hexwalk.hpp"
 #include "bgk_launch.hpp"
 
 using namespace bgk;
@@ -310,6 +311,7 @@ struct bgk_solver {
   std::vector<int> kinds;
   int cur = 0;  // state buffer (BF16 storage alternates between f(0) and f(1))
   int sweep_seg = 0;  // column sweeps of the RK stages: elements per work item (0: none)
+  int walk_tx = 0, walk_ty = 0, walk_ncols = 0;  // tile of the hexahedral walk (0: none)
   int xcd_part = 0;   // stage work items dealt to the XCDs chunk by chunk (xcd_chunk_remap)
   void* f(int b) const { return ws + L.f[b]; }
   void* state() const { return f(cur); }
@@ -418,6 +420,9 @@ StageArgs stage_args(const bgk_solver* s) {
   A.collide = s->pb.mu_ref > 0.0 ? 1 : 0;
   A.sweep_seg = s->sweep_seg;
   A.xcd_part = s->xcd_part;
+  A.walk_tx = s->walk_tx;
+  A.walk_ty = s->walk_ty;
+  A.walk_ncols = s->walk_ncols;
   for (int k = 0; k < 2; ++k)
     for (int sd = 0; sd < 2; ++sd) A.wall_off[k][sd] = -1;
   if (s->wall.nside) {
@@ -690,12 +695,8 @@ void init_solver(bgk_solver* s, const bgk_problem* pb, char* ws, hipStream_t str
   g.nv = s->L.nv;
   g.nvb = s->L.nvb;
   g.nchunk = s->L.nchunk;
-  // velocity slots: octants of the signs of the transported components. FP64
-  // hexahedra on the plane-split kernels keep the lexicographic order (no
-  // split): they measured 4 % faster with it on the 16^3 x 16^3 Taylor-Green
-  // box, where the one-lane FP32 hexahedra ran 6 % faster with the octants.
-  set_velocity_slots(g, !(pb->dim == 3 && pb->precision == BGK_FP64 &&
-                          !hex_one_lane(pb->order, pb->precision)));
+  // velocity slots: octants of the signs of the transported components
+  set_velocity_slots(g, true);
   build_ops(g.n1, g.dim, s->op);
   if (brick && pb->dim == 3) brick_order(g.nelem, s->order_host);
   if (brick) {
@@ -706,12 +707,20 @@ void init_solver(bgk_solver* s, const bgk_problem* pb, char* ws, hipStream_t str
       s->rcols_host[c] = row_cols(g, c * vb, (int)std::min<int64_t>((int64_t)(c + 1) * vb, g.nv));
   }
   setup_walls(s);
+  if (brick && pb->dim == 3 && !hex_one_lane(pb->order, pb->precision)) {
+    // the chunk whose rows take the most LDS
+    for (const RowCols& r : s->rcols_host)
+      if (!s->walk_ncols || HexWalk::rows_bytes(r.ncols) > HexWalk::rows_bytes(s->walk_ncols))
+        s->walk_ncols = r.ncols;
+    walk_tile(g, pb->precision, s->walk_ncols, &s->walk_tx, &s->walk_ty);
+  }
   if (brick) s->sweep_seg = sweep_segment(g, pb->precision, pb->mu_ref > 0.0);
   if (brick) {
     // XCDs sharing a velocity chunk in the stage launches (xcd_chunk_remap):
     // all eight for column sweeps (tgv3d FP32 3.15 against 3.25 ms per
-    // launch, box2d FP64 1 % faster), four for the plane-split hexahedra
-    // (tgv3d FP64 1.5 %, BF16 increments 1 % faster); contiguous ranges for
+    // launch, box2d FP64 1 % faster), four for the plane-split hexahedra (all
+    // z-layers of one tile column then sit on one XCD at 16 layers);
+    // contiguous ranges for
     // the per-element one-lane kernels (the Mach-2 box 2 % slower with eight).
     // BGK_XCD_PART overrides the choice (0: contiguous ranges).
     const char* env = getenv("BGK_XCD_PART");
