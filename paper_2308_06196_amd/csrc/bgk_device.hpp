@@ -144,6 +144,7 @@ struct StageArgs {
   int32_t rc_mask;
   int32_t sweep_seg;  // column sweeps: elements per work item along the last axis
   int32_t xcd_part;   // XCDs per chunk group of xcd_chunk_remap (else xcd_remap)
+  int32_t rows;  // 1: the RK stages run several elements per work-group (k_stage_rows)
   // hexahedral walk (k_stage_walk): elements per tile row, rows per tile, most
   // row entries per node of any velocity chunk
   int32_t walk_tx, walk_ty, walk_ncols;
@@ -623,7 +624,7 @@ __device__ __forceinline__ void element_partials_mfma(const CT (&fv)[NS], const 
                                                       double* __restrict__ partials,
                                                       int64_t node0, int64_t nx, int chunk,
                                                       unsigned char* stage, double* red,
-                                                      const int tid) {
+                                                      const int tid, const int nrows = NS) {
   constexpr int NR = part_rows<NS>();
   const int lane = tid & 63, wave = tid >> 6;
   double* ps = reinterpret_cast<double*>(stage) + wave * 64 * 5;
@@ -636,7 +637,7 @@ __device__ __forceinline__ void element_partials_mfma(const CT (&fv)[NS], const 
   ps[lane * 5 + 4] = vel.w * psi4;
   element_tiles<0, NS, ST, CT>(fv, gw, ps, red + wave * NR * 5, tid);
   lds_barrier();
-  for (int t = tid; t < 5 * NS; t += kBlock) {
+  for (int t = tid; t < 5 * nrows; t += kBlock) {
     const int node = t / 5, m = t - node * 5;
     double sum = red[node * 5 + m];
 #pragma unroll

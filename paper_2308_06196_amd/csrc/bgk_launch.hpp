@@ -26,6 +26,17 @@ int sweep_segment(const DevGeom& g, int precision, bool collide);
 // per node of any velocity chunk.
 hipError_t launch_walk(int precision, const StageArgs& A, hipStream_t s);
 void walk_tile(const DevGeom& g, int precision, int ncols, int* tx, int* ty);
+// Segments and low-order quadrilaterals: RK stage with several elements of a
+// mesh row per work-group (k_stage_rows). rows_pay: whether a solver of this
+// mesh uses it; rows_runs: work items per velocity chunk; rows_tab_bytes: LDS
+// of the equilibrium rows.
+bool rows_pay(const DevGeom& g, bool collide);
+int64_t rows_runs(const DevGeom& g);
+size_t rows_tab_bytes(const DevGeom& g, bool collide);
+hipError_t launch_rows(int precision, const StageArgs& A, hipStream_t s);
+hipError_t launch_rows_batch(int precision, int dim, int order, int stage, const StageArgs* args,
+                             const BatchList* list, size_t tab_bytes, unsigned grid,
+                             hipStream_t s);
 // mode 0: fused RK stage (a variant that does not read f^n when a = 0);
 // 1: residual L(f) in FP64; 2: moment partials only.
 hipError_t launch_stage(int precision, int mode, const StageArgs& A, hipStream_t s);

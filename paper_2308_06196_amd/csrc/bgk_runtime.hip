@@ -312,6 +312,7 @@ struct bgk_solver {
   int cur = 0;  // state buffer (BF16 storage alternates between f(0) and f(1))
   int sweep_seg = 0;  // column sweeps of the RK stages: elements per work item (0: none)
   int walk_tx = 0, walk_ty = 0, walk_ncols = 0;  // tile of the hexahedral walk (0: none)
+  bool rows = false;  // RK stages with several elements per work-group (k_stage_rows)
   int xcd_part = 0;   // stage work items dealt to the XCDs chunk by chunk (xcd_chunk_remap)
   void* f(int b) const { return ws + L.f[b]; }
   void* state() const { return f(cur); }
@@ -420,6 +421,7 @@ StageArgs stage_args(const bgk_solver* s) {
   A.collide = s->pb.mu_ref > 0.0 ? 1 : 0;
   A.sweep_seg = s->sweep_seg;
   A.xcd_part = s->xcd_part;
+  A.rows = s->rows;
   A.walk_tx = s->walk_tx;
   A.walk_ty = s->walk_ty;
   A.walk_ncols = s->walk_ncols;
@@ -714,6 +716,7 @@ void init_solver(bgk_solver* s, const bgk_problem* pb, char* ws, hipStream_t str
         s->walk_ncols = r.ncols;
     walk_tile(g, pb->precision, s->walk_ncols, &s->walk_tx, &s->walk_ty);
   }
+  if (brick) s->rows = rows_pay(g, pb->mu_ref > 0.0);
   if (brick) s->sweep_seg = sweep_segment(g, pb->precision, pb->mu_ref > 0.0);
   if (brick) {
     // XCDs sharing a velocity chunk in the stage launches (xcd_chunk_remap):
@@ -1294,16 +1297,16 @@ bgk_status bgk_residual_noalloc(const bgk_problem* pb, const double* f_in, doubl
 // their work units. A replay runs up to kSub sub-steps; each is three RK
 // stages of [equilibrium solves per team size, wall fluxes per family and wall
 // densities, one stage launch per kernel family (dimension, order, storage
-// precision)], every launch covering all members of its list, with the grid
+// precision, elements per work-group)], every launch covering all members of its list, with the grid
 // set to the list's work units. Admission and completion rewrite the tables
 // (copied on the batch stream, ahead of the launches that read them).
 // ---------------------------------------------------------------------------
 namespace {
 
 constexpr int kSub = 4;            // sub-steps per replay (a member takes up to 4 steps)
-constexpr int kMaxFamilies = 12;   // dimension 1-2 x order 1-3 x FP64/FP32
-// Stage work items (element x velocity chunk) from which a member fills the
-// device alone (32 work-groups per compute unit) and runs its RK stages with
+constexpr int kMaxFamilies = 24;   // dimension 1-2 x order 1-3 x FP64/FP32 x rows or not
+// (Element, velocity chunk) pairs from which a member fills the
+// device alone (32 per compute unit) and runs its RK stages with
 // its solo launches: the 2-D boxes of the serving mix above about 4e8 DOF
 // (the FP64 column sweep is some 8 % faster than the per-element items there).
 constexpr int64_t kSoloUnits = 8192;
@@ -1334,7 +1337,9 @@ TableLayout table_layout() {
 int team_index(int team) { return team == 16 ? 0 : team == 4 ? 1 : 2; }
 
 // work units of a member: stage work items, equilibrium work-groups
-int64_t member_units(const bgk_solver* s) { return s->L.ne * s->L.nchunk; }
+int64_t member_units(const bgk_solver* s) {
+  return (s->rows ? rows_runs(s->g) : s->L.ne) * s->L.nchunk;
+}
 int64_t member_newton_blocks(const bgk_solver* s) {
   return (s->L.nx * newton_team(s->L.nx) + 255) / 256;
 }
@@ -1361,6 +1366,7 @@ struct bgk_batch {
   };
   struct Family {
     int dim, order, precision;
+    bool rows;         // several elements per work item (k_stage_rows_batch)
     size_t tab_bytes;  // dynamic LDS of its stage launches (equilibrium rows)
   };
   struct Finished {
@@ -1431,7 +1437,7 @@ bgk_status upload_tables(bgk_batch* b) {
   static const double kB[3] = {1.0, 0.25, 2.0 / 3.0};
   for (auto& m : b->members) {
     bgk_solver* s = m.s;
-    m.solo = member_units(s) >= kSoloUnits;
+    m.solo = s->L.ne * s->L.nchunk >= kSoloUnits;
     // the arguments bgk_rk3_step passes for FP64/FP32 storage
     StageArgs A = stage_args(s);
     A.dt = m.dt;
@@ -1506,9 +1512,10 @@ bgk_status replay(bgk_batch* b) {
         e = launch_wall_rho_batch(stage, b->d_wargs(), b->d_list(sub, kAllList),
                                   (unsigned)b->units[sub][kAllList][3], b->stream);
       for (size_t f = 0; f < b->fams.size() && e == hipSuccess; ++f)
-        e = launch_stage_batch(b->fams[f].precision, b->fams[f].dim, b->fams[f].order, stage,
-                               b->d_args(), b->d_list(sub, (int)f), b->fams[f].tab_bytes,
-                               (unsigned)b->units[sub][f][0], b->stream);
+        e = (b->fams[f].rows ? launch_rows_batch : launch_stage_batch)(
+            b->fams[f].precision, b->fams[f].dim, b->fams[f].order, stage, b->d_args(),
+            b->d_list(sub, (int)f), b->fams[f].tab_bytes, (unsigned)b->units[sub][f][0],
+            b->stream);
       for (size_t i = 0; i < b->members.size() && e == hipSuccess; ++i) {
         const bgk_batch::Member& m = b->members[i];
         if (m.solo && m.per_replay > sub)
@@ -1656,12 +1663,14 @@ bgk_status bgk_batch_add(bgk_batch* b, bgk_solver* s, double dt, int64_t nsteps)
   int fam = -1;
   for (size_t f = 0; f < b->fams.size(); ++f)
     if (b->fams[f].dim == s->pb.dim && b->fams[f].order == s->pb.order &&
-        b->fams[f].precision == s->precision)
+        b->fams[f].precision == s->precision && b->fams[f].rows == s->rows)
       fam = (int)f;
-  const size_t tab = s->pb.mu_ref > 0.0 ? (size_t)s->L.ns * s->g.tabw * sizeof(double) : 0;
+  const size_t tab = s->rows ? rows_tab_bytes(s->g, s->pb.mu_ref > 0.0)
+                     : s->pb.mu_ref > 0.0 ? (size_t)s->L.ns * s->g.tabw * sizeof(double)
+                                          : 0;
   if (fam < 0) {
     if ((int)b->fams.size() >= kMaxFamilies) return fail(BGK_ERR_UNSUPPORTED, "too many families");
-    b->fams.push_back({s->pb.dim, s->pb.order, s->precision, tab});
+    b->fams.push_back({s->pb.dim, s->pb.order, s->precision, s->rows, tab});
     fam = (int)b->fams.size() - 1;
   }
   b->fams[fam].tab_bytes = std::max(b->fams[fam].tab_bytes, tab);
