@@ -429,6 +429,27 @@ __device__ __forceinline__ float sreg(float x) {
 }
 __device__ __forceinline__ int sreg(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+// Source of a kernel's distribution values: the internal state (storage
+// precision ST, nodes kVB entries apart) or, with CAN, a canonical FP64 array
+// f[elem][node][vel] in lexicographic velocity order (the kernel's arguments
+// then carry a single octant), whose values are rounded to ST on the read.
+template <bool CAN, typename ST>
+struct Source {
+  using T = ST;
+  static __device__ __forceinline__ int64_t stride(const DevGeom&) { return kVB; }
+  static __device__ __forceinline__ int64_t offset(const DevGeom& g, int64_t e, int a, int64_t j) {
+    return f_offset(g, e, a, j);
+  }
+};
+template <typename ST>
+struct Source<true, ST> {
+  using T = double;
+  static __device__ __forceinline__ int64_t stride(const DevGeom& g) { return g.nv; }
+  static __device__ __forceinline__ int64_t offset(const DevGeom& g, int64_t e, int a, int64_t j) {
+    return (e * g.ns + a) * g.nv + j;
+  }
+};
+
 template <typename ST> struct Compute;
 template <> struct Compute<double> { using T = double; };
 template <> struct Compute<float> { using T = float; };
@@ -492,6 +513,29 @@ __device__ __forceinline__ RowPick row_pick(const StageArgs& A, int chunk, int n
   r.ncols = rc.ncols;
   r.magic = (uint32_t)rc.magic;
   r.count = ns * rc.ncols;
+  return r;
+}
+
+// The entries that `vb` consecutive slots of chunk `chunk` use in lexicographic
+// velocity order: whole axes where the slots wrap around them.
+__device__ __forceinline__ RowPick row_pick_lexicographic(const StageArgs& A, int chunk, int vb,
+                                                          int ns) {
+  const DevGeom& g = A.g;
+  const int j0 = chunk * vb, j1 = min(j0 + vb, (int)g.nv) - 1;
+  const int r0 = j0 / g.nv1[0], r1 = j1 / g.nv1[0], z0 = r0 / g.nv1[1], z1 = r1 / g.nv1[1];
+  RowPick r;
+  r.S = g.tabw;
+  r.x0 = r0 == r1 ? j0 - r0 * g.nv1[0] : 0;
+  r.nx = r0 == r1 ? j1 - j0 + 1 : g.nv1[0];
+  r.y0 = z0 == z1 ? r0 - z0 * g.nv1[1] : 0;
+  r.nxy = r.nx + (z0 == z1 ? r1 - r0 + 1 : g.nv1[1]);
+  r.z0 = z0;
+  r.nxyz = r.nxy + z1 - z0 + 1;
+  r.oy = g.nv1[0] + r.y0;
+  r.oz = g.nv1[0] + g.nv1[1] + r.z0;
+  r.ncols = r.nxyz + 1;
+  r.magic = 0xFFFFFFFFu / (uint32_t)r.ncols + 1u;  // ceil(2^32 / ncols), ncols >= 4
+  r.count = ns * r.ncols;
   return r;
 }
 
@@ -831,13 +875,16 @@ template <int DIM, int P>
 constexpr int sweep_tr_regs() {
   return DIM == 2 ? P + 1 : 1;
 }
-template <int DIM, int P, typename ST, int MODE, bool INC = false, bool SW = false>
+template <int DIM, int P, typename ST, int MODE, bool INC = false, bool SW = false,
+          bool CAN = false>
 __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, const int64_t e,
                                            const bool count, const bool carry, const bool up,
                                            typename Compute<ST>::T (&tr)[sweep_tr_regs<DIM, P>()]) {
   static_assert(!INC || (MODE != 1 && sizeof(ST) == 4), "increment stages: FP32 state, RK modes");
   static_assert(!SW || (DIM >= 2 && MODE != 1), "column sweeps: quadrilaterals and hexahedra, RK modes");
+  static_assert(!CAN || MODE == 1, "canonical source: residual");
   using CT = typename Compute<ST>::T;
+  using Src = Source<CAN, ST>;
   // FR line contractions on the matrix cores for FP32 arithmetic on p = 3
   // hexahedra (measured 2-4 % faster there); segments, quadrilaterals and
   // p < 3 hexahedra keep them on the VALU, which measured faster (2-D box:
@@ -898,8 +945,10 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   // (u_k > 0), its left trace (u_k < 0), or the own trace on the wall side.
   // At a diffuse wall the exterior state is the re-emitted wall Maxwellian
   // (dif[k]; the loads then read the own element and go unused).
-  const ST* __restrict__ fin = (const ST*)A.fin;
-  const ST* src[DIM];
+  using FT = typename Src::T;
+  const int64_t nst = Src::stride(g);  // between the nodes of an element
+  const FT* __restrict__ fin = (const FT*)A.fin;
+  const FT* src[DIM];
   bool pos[DIM], use_right[DIM], dif[DIM], wall_in[DIM][2];
 #pragma unroll
   for (int k = 0; k < DIM; ++k) {
@@ -930,7 +979,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
       src_e = e + (int64_t)(nk - ek[k]) * stride;
     }
     use_right[k] = (pos[k] != wall);
-    src[k] = fin + f_offset(g, src_e, 0, src_j);
+    src[k] = fin + Src::offset(g, src_e, 0, src_j);
   }
   // sweep: lanes whose upwind neighbour on axis KS is the previous element of
   // the column take its carried traces; a wave loads that neighbour's nodes
@@ -952,7 +1001,8 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   // after the transport. Every lane loads (clamped index, no branch): a
   // conditional load makes the compiler wait for it right there.
   constexpr int kU = 2;  // covers the row entries of a 1-D or 2-D chunk (ns x ncols <= 512)
-  const RowPick rp = row_pick(A, chunk, NS);
+  const RowPick rp =
+      CAN ? row_pick_lexicographic(A, chunk, kBlock, NS) : row_pick(A, chunk, NS);
   const double* et = A.etab + node0 * S;
   double tv[kU];
   if (A.collide) {
@@ -969,11 +1019,11 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   constexpr bool kDin = INC && MODE == 0;
   constexpr bool kKeepF = INC && NS <= 16;
   const uint16_t* __restrict__ din = A.din;
-  const ST* fe = fin + f_offset(g, e, 0, jj);
+  const FT* fe = fin + Src::offset(g, e, 0, jj);
   CT f[NS];
   CT fb[kKeepF ? NS : 1];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) f[i] = (CT)fe[i * kVB];
+  for (int i = 0; i < NS; ++i) f[i] = (CT)(ST)fe[i * nst];
   if constexpr (kKeepF) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) fb[i] = f[i];
@@ -982,7 +1032,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   CT nbv[kPreload ? DIM : 1][kPreload ? NS : 1];
   if constexpr (kPreload) {
 #pragma unroll
-    for (int i = 0; i < NS; ++i) nbv[0][i] = (CT)src[0][i * kVB];
+    for (int i = 0; i < NS; ++i) nbv[0][i] = (CT)(ST)src[0][i * nst];
     if constexpr (kDin) add_increments(nbv[0], din, src[0] - fin);
   }
   // the needed entries of this element's equilibrium rows -> LDS
@@ -1010,7 +1060,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
         __builtin_amdgcn_sched_barrier(0);
         if (ld) {
 #pragma unroll
-          for (int i = 0; i < NS; ++i) nbv[k][i] = (CT)src[k][i * kVB];
+          for (int i = 0; i < NS; ++i) nbv[k][i] = (CT)(ST)src[k][i * nst];
           if constexpr (kDin) add_increments(nbv[k], din, src[k] - fin);
         }
       }
@@ -1020,7 +1070,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
       if constexpr (kPreload) {
         return nbv[k][i];
       } else {
-        CT xv = (CT)src[k][i * kVB];
+        CT xv = (CT)(ST)src[k][i * nst];
         if constexpr (kDin) xv += increment_of<NS>(din, src[k] - fin, i);
         return xv;
       }
@@ -1352,6 +1402,19 @@ __global__ void __launch_bounds__(kBlock)
                                     w == 0, false, false, tr);
 }
 
+// Residual L(f) of a canonical FP64 array (see Source).
+template <int DIM, int P, typename ST>
+__global__ void __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(stage_waves<DIM, P, typename Compute<ST>::T, false>())))
+    k_residual(const StageArgs A) {
+  const int64_t w = xcd_chunk_remap(blockIdx.x, gridDim.x, A.ecount, A.xcd_part);
+  typename Compute<ST>::T tr[sweep_tr_regs<DIM, P>()];
+  stage_item<DIM, P, ST, 1, false, false, true>(A, (int)(w / A.ecount),
+                                                work_element(A.order, A.e0, w, A.ecount), w == 0,
+                                                false, false, tr);
+}
+
+
 // Pointer into argument memory that is read-only while kernels run (kernel
 // arguments, descriptor tables): loads through the constant address space
 // become scalar loads that the compiler may repeat where a value is used,
@@ -1471,10 +1534,12 @@ __global__ void __launch_bounds__(kBlock)
                                w == 0, false, false, tr);
 }
 
-// Moment partials of a stored state (first stage after installation).
-template <int DIM, int P, typename ST>
+// Moment partials of a stored state (first stage after installation) or, with
+// CAN, of a canonical FP64 array.
+template <int DIM, int P, typename ST, bool CAN = false>
 __global__ void __launch_bounds__(kBlock) k_moments(const StageArgs A) {
   using CT = typename Compute<ST>::T;
+  using Src = Source<CAN, ST>;
   constexpr int N1 = P + 1;
   constexpr int NS = ipow(N1, DIM);
   __shared__ double red[(kBlock / 64) * part_rows<NS>() * 5];
@@ -1489,10 +1554,11 @@ __global__ void __launch_bounds__(kBlock) k_moments(const StageArgs A) {
   const int jj = valid ? j : (int)nv - 1;
   Vel vel = velocity_of(g, jj);
   if (!valid) vel.w = 0.0;
-  const ST* fe = (const ST*)A.fin + f_offset(g, e, 0, jj);
+  const typename Src::T* fe = (const typename Src::T*)A.fin + Src::offset(g, e, 0, jj);
+  const int64_t nst = Src::stride(g);
   CT f[NS];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) f[i] = (CT)fe[i * kVB];
+  for (int i = 0; i < NS; ++i) f[i] = (CT)(ST)fe[i * nst];
   element_partials_mfma<NS, ST, CT>(f, vel, A.partials, e * NS, g.nx, chunk, dyn_lds, red,
                                     (int)threadIdx.x);
 }

@@ -91,12 +91,15 @@ __device__ __forceinline__ void plane_partials_mfma(const CT (&fv)[Plane3<P>::P2
 }
 
 
-// One work item (element e x velocity chunk) of the residual L(f) in FP64 (the
+// One work item (element e x velocity chunk) of the residual L(f) in FP64, of
+// the internal state or a canonical array (see Source; the
 // RK stages of these elements are k_stage_walk's, bgk_hexwalk.hpp).
-template <int P, typename ST>
+template <int P, typename ST, bool CAN>
 __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chunk, const int64_t e,
                                                const bool count) {
   using CT = typename Compute<ST>::T;
+  using Src = Source<CAN, ST>;
+  using FT = typename Src::T;
   using PL = Plane3<P>;
   constexpr bool kMfma = sizeof(CT) == 4;
   constexpr int N1 = PL::N1, G = PL::G, VB = PL::VB, P2 = PL::P2, NS = PL::NS;
@@ -133,8 +136,9 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
       r /= g.nelem[k];
     }
   }
-  const ST* __restrict__ fin = (const ST*)A.fin;
-  const ST* src[3];
+  const int64_t nst = Src::stride(g);
+  const FT* __restrict__ fin = (const FT*)A.fin;
+  const FT* src[3];
   bool pos[3], use_right[3], wall_in[3][2];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -161,14 +165,14 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
       src_e = e + (int64_t)(nk - ek[k]) * stride;
     }
     use_right[k] = (pos[k] != wall);
-    src[k] = fin + f_offset(g, src_e, pl * P2, src_j);
+    src[k] = fin + Src::offset(g, src_e, pl * P2, src_j);
   }
 
   // first batch of row loads: 4 x 256 entries for FP32 arithmetic, whose
   // registers are scarcer, 6 x 256 in FP64 (a 64-velocity chunk of the 16^3
   // grid at p = 3 needs 64 x 18 or more)
   constexpr int kU = kMfma ? 4 : 6;
-  const RowPick rp = row_pick(A, chunk, NS);
+  const RowPick rp = CAN ? row_pick_lexicographic(A, chunk, VB, NS) : row_pick(A, chunk, NS);
   const double* et = A.etab + node0 * S;
   double tv[kU];
   if (A.collide) {
@@ -178,12 +182,12 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
       tv[u] = et[rp.offset(t < rp.count ? t : rp.count - 1)];
     }
   }
-  const ST* fe = fin + f_offset(g, e, pl * P2, jj);
+  const FT* fe = fin + Src::offset(g, e, pl * P2, jj);
   CT f[P2], nb[P2];
 #pragma unroll
-  for (int q = 0; q < P2; ++q) f[q] = (CT)fe[q * kVB];
+  for (int q = 0; q < P2; ++q) f[q] = (CT)(ST)fe[q * nst];
 #pragma unroll
-  for (int q = 0; q < P2; ++q) nb[q] = (CT)src[0][q * kVB];
+  for (int q = 0; q < P2; ++q) nb[q] = (CT)(ST)src[0][q * nst];
   if (A.collide) {
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
@@ -205,7 +209,7 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
     if (k > 0) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 0; q < P2; ++q) nb[q] = (CT)src[k][q * kVB];
+      for (int q = 0; q < P2; ++q) nb[q] = (CT)(ST)src[k][q * nst];
     }
     const int S1 = k == 0 ? 1 : N1;
     const CT a = (CT)(vel.u[k] * g.scale[k]);
@@ -269,7 +273,7 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int q = 0; q < P2; ++q) nb[q] = (CT)src[2][q * kVB];
+  for (int q = 0; q < P2; ++q) nb[q] = (CT)(ST)src[2][q * nst];
   // z: the column of node q is spread over the group's lanes; lane lp holds
   // plane lp and its partners lane ^ r the other planes. The derivative is
   // sum_r D[lp][lp ^ r] f(lp ^ r); the trace difference ext - own is one
@@ -326,16 +330,17 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
 
 // Three waves per SIMD in FP64, four in FP32 arithmetic (the neighbours'
 // planes loaded one axis at a time).
-template <int P, typename ST>
+template <int P, typename ST, bool CAN>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(sizeof(ST) == 8 ? 3 : 4))) k_residual3(const StageArgs A) {
   const int64_t w = xcd_chunk_remap(blockIdx.x, gridDim.x, A.ecount, A.xcd_part);
-  residual3_item<P, ST>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount), w == 0);
+  residual3_item<P, ST, CAN>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount), w == 0);
 }
 
-template <int P, typename ST>
+template <int P, typename ST, bool CAN>
 __global__ void __launch_bounds__(kBlock) k_moments3(const StageArgs A) {
   using CT = typename Compute<ST>::T;
+  using Src = Source<CAN, ST>;
   using PL = Plane3<P>;
   constexpr int N1 = PL::N1, G = PL::G, VB = PL::VB, P2 = PL::P2, NS = PL::NS;
   __shared__ double red[(kBlock / 64) * NS * 5];
@@ -353,10 +358,11 @@ __global__ void __launch_bounds__(kBlock) k_moments3(const StageArgs A) {
   const int jj = valid ? j : (int)nv - 1;
   Vel vel = velocity_of(g, jj);
   if (!(valid && live)) vel.w = 0.0;
-  const ST* fe = (const ST*)A.fin + f_offset(g, e, pl * P2, jj);
+  const typename Src::T* fe = (const typename Src::T*)A.fin + Src::offset(g, e, pl * P2, jj);
+  const int64_t nst = Src::stride(g);
   CT f[P2];
 #pragma unroll
-  for (int q = 0; q < P2; ++q) f[q] = (CT)fe[q * kVB];
+  for (int q = 0; q < P2; ++q) f[q] = (CT)(ST)fe[q * nst];
   plane_partials_mfma<P, ST, CT>(f, vel, A.partials, e * NS, g.nx, chunk, lp, dyn_lds, red,
                                  (int)threadIdx.x);
 }

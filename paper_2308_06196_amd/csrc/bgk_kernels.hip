@@ -363,8 +363,9 @@ __global__ void __launch_bounds__(kBlock) k_collision_moments(const StageArgs A,
 // One work-group = one wall-face element x one chunk of 256 velocities; the
 // flux points' partial sums are reduced in a fixed order (lanes by an xor
 // butterfly, then the four waves in LDS).
-template <int DIM, int P, typename ST>
+template <int DIM, int P, typename ST, bool CAN = false>
 __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
+  using Src = Source<CAN, ST>;
   constexpr int N1 = P + 1;
   constexpr int NF = ipow(N1, DIM - 1);
   __shared__ double red[kBlock / 64][NF];
@@ -388,7 +389,8 @@ __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
   const bool outgoing = valid && (side == 0 ? a < 0.0 : a > 0.0);
   const double wt = outgoing ? vel.w * fabs(a) : 0.0;
   const int S1 = k == 0 ? 1 : N1;
-  const ST* fe = (const ST*)W.fin + f_offset(g, e, 0, jj);
+  const typename Src::T* fe = (const typename Src::T*)W.fin + Src::offset(g, e, 0, jj);
+  const int64_t nst = Src::stride(g);
   double v[NF];
 #pragma unroll
   for (int fp = 0; fp < NF; ++fp) {
@@ -396,7 +398,7 @@ __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
     double tr = 0.0;
 #pragma unroll
     for (int bb = 0; bb < N1; ++bb)
-      tr += (side == 0 ? W.lamL[bb] : W.lamR[bb]) * (double)fe[(base + bb * S1) * kVB];
+      tr += (side == 0 ? W.lamL[bb] : W.lamR[bb]) * (double)(ST)fe[(base + bb * S1) * nst];
     v[fp] = wt * tr;
   }
 #pragma unroll
@@ -418,9 +420,9 @@ __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
   }
 }
 
-template <int DIM, int P, typename ST>
+template <int DIM, int P, typename ST, bool CAN>
 __global__ void __launch_bounds__(kBlock) k_wall_flux(const WallArgs W) {
-  wall_flux_item<DIM, P, ST>(W, blockIdx.x);
+  wall_flux_item<DIM, P, ST, CAN>(W, blockIdx.x);
 }
 
 template <int DIM, int P, typename ST>
@@ -580,8 +582,12 @@ static hipError_t hex_dispatch(int mode, bool inc, const StageArgs& A, size_t ta
         hipLaunchKernelGGL((k_stage<3, P, ST, 3>), grid, block, lds, s, A);
       } else if (mode == 1) {
         hipLaunchKernelGGL((k_stage<3, P, ST, 1>), grid, block, lds, s, A);
-      } else {
+      } else if (mode == 2) {
         hipLaunchKernelGGL((k_moments<3, P, ST>), grid, block, lds, s, A);
+      } else if (mode == 3) {
+        hipLaunchKernelGGL((k_residual<3, P, ST>), grid, block, lds, s, A);
+      } else {
+        hipLaunchKernelGGL((k_moments<3, P, ST, true>), grid, block, lds, s, A);
       }
       return hipGetLastError();
     }
@@ -589,10 +595,13 @@ static hipError_t hex_dispatch(int mode, bool inc, const StageArgs& A, size_t ta
   if constexpr (P == 3) {  // plane-split: FP64 storage, BF16 increments
     if (mode == 0) return launch_walk(sizeof(ST) == 8 ? 0 : 2, A, s);
     if (mode == 1) {
-      hipLaunchKernelGGL((k_residual3<P, ST>), grid, block, tab, s, A);
+      hipLaunchKernelGGL((k_residual3<P, ST, false>), grid, block, tab, s, A);
+    } else if (mode == 3) {
+      hipLaunchKernelGGL((k_residual3<P, ST, true>), grid, block, tab, s, A);
     } else {
       const size_t lds3 = std::max(tab, (size_t)mfma3_lds_bytes<P, ST>());
-      hipLaunchKernelGGL((k_moments3<P, ST>), grid, block, lds3, s, A);
+      if (mode == 2) hipLaunchKernelGGL((k_moments3<P, ST, false>), grid, block, lds3, s, A);
+      else hipLaunchKernelGGL((k_moments3<P, ST, true>), grid, block, lds3, s, A);
     }
     return hipGetLastError();
   }
@@ -606,7 +615,7 @@ static hipError_t stage_dispatch(int mode, bool inc, const StageArgs& A, hipStre
   // dynamic LDS: equilibrium rows (relaxation), then, in the 1-D/2-D
   // kernels, the MFMA staging of the moment partials in the same bytes
   const size_t tab = A.collide ? (size_t)A.g.ns * A.g.tabw * sizeof(double) : 0;
-  const size_t lds = mode != 1 ? std::max(tab, (size_t)mfma_lds_bytes<ST>()) : tab;
+  const size_t lds = mode != 1 && mode != 3 ? std::max(tab, (size_t)mfma_lds_bytes<ST>()) : tab;
 #define BGK_CASE(D, P)                                                     \
   case D * 10 + P:                                                         \
     if (D >= 2 && use_sweep(mode, A)) {                                    \
@@ -628,8 +637,12 @@ static hipError_t stage_dispatch(int mode, bool inc, const StageArgs& A, hipStre
       hipLaunchKernelGGL((k_stage<D, P, ST, 3>), grid, block, lds, s, A);  \
     else if (mode == 1)                                                    \
       hipLaunchKernelGGL((k_stage<D, P, ST, 1>), grid, block, lds, s, A);  \
-    else                                                                   \
+    else if (mode == 2)                                                    \
       hipLaunchKernelGGL((k_moments<D, P, ST>), grid, block, lds, s, A);   \
+    else if (mode == 3)                                                    \
+      hipLaunchKernelGGL((k_residual<D, P, ST>), grid, block, lds, s, A);  \
+    else                                                                   \
+      hipLaunchKernelGGL((k_moments<D, P, ST, true>), grid, block, lds, s, A); \
     break;
 #define BGK_CASE3(P)                                                       \
   case 30 + P:                                                             \
@@ -758,12 +771,15 @@ hipError_t launch_stage(int precision, int mode, const StageArgs& A, hipStream_t
 }
 
 template <typename ST>
-static hipError_t wall_dispatch(const WallArgs& W, hipStream_t s) {
+static hipError_t wall_dispatch(bool canonical, const WallArgs& W, hipStream_t s) {
   const dim3 grid((unsigned)W.blk0[W.nside]), block(kBlock);
   switch (W.g.dim * 10 + (W.g.n1 - 1)) {
 #define BGK_WALL(D, P)                                                          \
   case D * 10 + P:                                                              \
-    hipLaunchKernelGGL((k_wall_flux<D, P, ST>), grid, block, 0, s, W);          \
+    if (canonical)                                                              \
+      hipLaunchKernelGGL((k_wall_flux<D, P, ST, true>), grid, block, 0, s, W);  \
+    else                                                                        \
+      hipLaunchKernelGGL((k_wall_flux<D, P, ST, false>), grid, block, 0, s, W); \
     break;
     BGK_WALL(1, 1) BGK_WALL(1, 2) BGK_WALL(1, 3)
     BGK_WALL(2, 1) BGK_WALL(2, 2) BGK_WALL(2, 3)
@@ -777,9 +793,10 @@ static hipError_t wall_dispatch(const WallArgs& W, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_wall(int precision, const WallArgs& W, hipStream_t s) {
+hipError_t launch_wall(int precision, bool canonical, const WallArgs& W, hipStream_t s) {
   if (W.nside == 0) return hipSuccess;
-  return precision == 0 ? wall_dispatch<double>(W, s) : wall_dispatch<float>(W, s);
+  return precision == 0 ? wall_dispatch<double>(canonical, W, s)
+                        : wall_dispatch<float>(canonical, W, s);
 }
 
 hipError_t launch_newton(const NewtonArgs& A, hipStream_t s) {

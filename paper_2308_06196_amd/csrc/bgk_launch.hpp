@@ -38,11 +38,14 @@ hipError_t launch_rows_batch(int precision, int dim, int order, int stage, const
                              const BatchList* list, size_t tab_bytes, unsigned grid,
                              hipStream_t s);
 // mode 0: fused RK stage (a variant that does not read f^n when a = 0);
-// 1: residual L(f) in FP64; 2: moment partials only.
+// 1: residual L(f) in FP64; 2: moment partials only; 3, 4: the same two of a
+// canonical FP64 array A.fin in lexicographic velocity order (A.g with a single
+// octant).
 hipError_t launch_stage(int precision, int mode, const StageArgs& A, hipStream_t s);
 hipError_t launch_newton(const NewtonArgs& A, hipStream_t s);
 // Re-emitted densities of the diffuse-wall flux points of the stage input.
-hipError_t launch_wall(int precision, const WallArgs& W, hipStream_t s);
+// canonical: W.fin is a canonical FP64 array (W.g with a single octant).
+hipError_t launch_wall(int precision, bool canonical, const WallArgs& W, hipStream_t s);
 hipError_t launch_reduce_partials(const DevGeom& g, const double* partials, double* Q,
                                   hipStream_t s);
 // Moments of the collision term of the stage input A.fin into Cm[nx][5]

@@ -491,7 +491,7 @@ bgk_status wall_densities(bgk_solver* s, const void* fin, hipStream_t st) {
   if (!s->wall.nside) return BGK_OK;
   WallArgs W = s->wall;
   W.fin = fin;
-  HIP_TRY(launch_wall(s->precision, W, st));
+  HIP_TRY(launch_wall(s->precision, false, W, st));
   return BGK_OK;
 }
 
@@ -577,6 +577,35 @@ void brick_order(const int32_t* ne, std::vector<int32_t>& out) {
           for (int y = by; y < std::min(by + B, ne[1]); ++y)
             for (int x = bx; x < std::min(bx + B, ne[0]); ++x)
               out.push_back(x + ne[0] * (y + ne[1] * z));
+}
+
+// Residual L(f_in) of a canonical device array that r_out does not overlap:
+// moments, equilibria, wall densities and residual read f_in in place, in its
+// own velocity order, so nothing is converted first and the residual's rows
+// are written whole.
+bgk_status residual_canonical(bgk_solver* s, const double* f_in, double* r_out) {
+  StageArgs A = stage_args(s);
+  set_velocity_slots(A.g, false);
+  A.fin = f_in;
+  A.out = r_out;
+  HIP_TRY(launch_stage(s->precision, 4, A, s->stream));
+  NewtonArgs N = newton_args(s);
+  N.Q = nullptr;
+  HIP_TRY(launch_newton(N, s->stream));
+  if (s->wall.nside) {
+    WallArgs W = s->wall;
+    W.g = A.g;
+    W.fin = f_in;
+    HIP_TRY(launch_wall(s->precision, true, W, s->stream));
+  }
+  HIP_TRY(launch_stage(s->precision, 3, A, s->stream));
+  return BGK_OK;
+}
+
+// Whether two arrays of n doubles share memory.
+bool overlap(const double* a, const double* b, int64_t n) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b, m = (uintptr_t)n * 8;
+  return x < y + m && y < x + m;
 }
 
 bgk_status moments_of(bgk_solver* s, const void* fstore) {
@@ -911,6 +940,10 @@ bgk_status bgk_residual(bgk_solver* s, const double* f_in, double* r_out, int32_
   }
   const int64_t n = s->L.nx * s->L.nv;
   const void* fin = s->state();
+  if (f_in && where == BGK_DEVICE && !overlap(f_in, r_out, n)) {
+    s->partials_valid = false;  // the partials now belong to f_in
+    return residual_canonical(s, f_in, r_out);
+  }
   if (f_in) {
     // f_in goes to the state-precision buffer that does not hold the state
     void* dst = s->f(1 - s->cur);
@@ -1275,6 +1308,7 @@ bgk_status bgk_residual_noalloc(const bgk_problem* pb, const double* f_in, doubl
                      row_cols_all(s.g));
   HIP_TRY(hipGetLastError());
   const int64_t n = L.nx * L.nv;
+  if (!overlap(f_in, r_out, n)) return residual_canonical(&s, f_in, r_out);
   HIP_TRY(launch_to_storage(s.precision, s.g, f_in, s.f(0), 0, n, s.stream));
   if ((st = moments_of(&s, s.f(0)))) return st;
   NewtonArgs N = newton_args(&s);
