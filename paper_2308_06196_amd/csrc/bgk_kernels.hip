@@ -458,49 +458,95 @@ __global__ void __launch_bounds__(256) k_wall_rho_batch(table_ptr<WallArgs> args
                 (int)((t - list->wrho_off[m]) * 256 + threadIdx.x));
 }
 
-// Continuous Maxwellian sampled at every (node, velocity); one work-group =
-// one node x one velocity chunk.
-// grid-stride over (node, velocity chunk) work items: the number of work
-// items can exceed what one launch dimension holds
-template <typename ST>
-__global__ void __launch_bounds__(kBlock) k_maxwellian(const DevGeom g, const double* prim, ST* f) {
-  const int64_t nw = g.nx * g.nchunk;
-  for (int64_t w = blockIdx.x; w < nw; w += gridDim.x) {
-    const int64_t node = w / g.nchunk;
-    const int chunk = (int)(w % g.nchunk);
-    const int j = chunk * kBlock + (int)threadIdx.x;
-    if (j >= g.nv) continue;
-    const Vel v = velocity_of(g, j);
-    const double* q = prim + node * 5;
-    const double rho = q[0], th = q[4];
-    const double nrm = rho / pow(2.0 * M_PI * th, 1.5);
-    const double dx = v.u[0] - q[1], dy = v.u[1] - q[2], dz = v.u[2] - q[3];
-    f[f_offset(g, node / g.ns, (int)(node % g.ns), j)] =
-        (ST)(nrm * exp(-(dx * dx + dy * dy + dz * dz) / (2.0 * th)));
-  }
-}
-
 // Exchange between the canonical FP64 layout f[elem][node][vel] and the
 // internal layout in storage precision (velocity blocks, velocities in slot
-// order): entries i0 .. i0+m-1 of the canonical
-// array, held at canon[0 .. m-1] (a staging window or the whole array).
+// order): entries i0 .. i0+m-1 of the canonical array, held at canon[0 .. m-1]
+// (a staging window or the whole array). One work-group = kXNodes consecutive
+// nodes from n0 on x 256 velocities; a lane decodes its velocity once and
+// walks the nodes (one entry per lane and iteration, with its two divisions,
+// took 1.00 ms for the FP32 state of the 32^2 box, 2.7 TB/s; this 0.52, 5.3
+// TB/s; FP64 state of the 16^3-element Taylor-Green box 4.53 -> 2.89 ms, 5.95
+// TB/s: HBM-bound). Lanes follow
+// the written order, so that stores are whole lines; the gathered side's
+// partial lines meet in the L2 of the XCD that runs the neighbouring chunks.
+constexpr int kXNodes = 16;
+
+struct XItem {
+  int64_t n;  // first node
+  int j;      // velocity of this lane in the written order
+};
+__device__ __forceinline__ XItem exchange_item(const DevGeom& g, int64_t n0) {
+  const int64_t nch = (g.nv + kBlock - 1) / kBlock;
+  const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t r = w / nch;
+  return {n0 + r * kXNodes, (int)(w - r * nch) * kBlock + (int)threadIdx.x};
+}
+
 template <typename DST>
-__global__ void __launch_bounds__(256) k_to_internal(const DevGeom g, const double* canon, DST* f,
-                                                     int64_t i0, int64_t m) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x, per_e = (int64_t)g.ns * g.nv;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < m; t += stride) {
-    const int64_t i = i0 + t, e = i / per_e, r = i - e * per_e, a = r / g.nv;
-    f[f_offset(g, e, (int)a, vel_slot_of_canonical(g, (int)(r - a * g.nv)))] = (DST)canon[t];
+__global__ void __launch_bounds__(kBlock) k_to_internal(const DevGeom g, const double* canon,
+                                                        DST* f, int64_t i0, int64_t m, int64_t n0) {
+  const XItem x = exchange_item(g, n0);
+  if (x.j >= g.nv) return;
+  int b[3];
+  slot_nodes(g, x.j, b);
+  const int jc = b[0] + g.nv1[0] * (b[1] + g.nv1[1] * b[2]);
+  double v[kXNodes];
+#pragma unroll
+  for (int q = 0; q < kXNodes; ++q) {
+    const int64_t t = (x.n + q) * g.nv + jc - i0;
+    v[q] = canon[t < 0 ? 0 : t < m ? t : m - 1];
+  }
+#pragma unroll
+  for (int q = 0; q < kXNodes; ++q) {
+    const int64_t n = x.n + q, t = n * g.nv + jc - i0, e = n / g.ns;
+    if (t >= 0 && t < m) f[f_offset(g, e, (int)(n - e * g.ns), x.j)] = (DST)v[q];
   }
 }
 
 template <typename SRC>
-__global__ void __launch_bounds__(256) k_to_canonical(const DevGeom g, const SRC* f, double* canon,
-                                                      int64_t i0, int64_t m) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x, per_e = (int64_t)g.ns * g.nv;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < m; t += stride) {
-    const int64_t i = i0 + t, e = i / per_e, r = i - e * per_e, a = r / g.nv;
-    canon[t] = (double)f[f_offset(g, e, (int)a, vel_slot_of_canonical(g, (int)(r - a * g.nv)))];
+__global__ void __launch_bounds__(kBlock) k_to_canonical(const DevGeom g, const SRC* f,
+                                                         double* canon, int64_t i0, int64_t m,
+                                                         int64_t n0) {
+  const XItem x = exchange_item(g, n0);
+  if (x.j >= g.nv) return;
+  const int slot = vel_slot_of_canonical(g, x.j);
+  SRC v[kXNodes];
+#pragma unroll
+  for (int q = 0; q < kXNodes; ++q) {
+    const int64_t n = x.n + q < g.nx ? x.n + q : g.nx - 1, e = n / g.ns;
+    v[q] = f[f_offset(g, e, (int)(n - e * g.ns), slot)];
+  }
+#pragma unroll
+  for (int q = 0; q < kXNodes; ++q) {
+    const int64_t t = (x.n + q) * g.nv + x.j - i0;
+    if (t >= 0 && t < m) __builtin_nontemporal_store((double)v[q], &canon[t]);
+  }
+}
+
+// Continuous Maxwellian sampled at every (node, velocity), by the exchange
+// kernels' work items; the nodes' normalisations (a power each) are formed
+// once per work-group.
+template <typename ST>
+__global__ void __launch_bounds__(kBlock) k_maxwellian(const DevGeom g, const double* prim, ST* f) {
+  __shared__ double nrm[kXNodes];
+  const XItem x = exchange_item(g, 0);
+  if (threadIdx.x < kXNodes) {
+    const int64_t n = x.n + threadIdx.x;
+    const double* q = prim + (n < g.nx ? n : g.nx - 1) * 5;
+    nrm[threadIdx.x] = q[0] / pow(2.0 * M_PI * q[4], 1.5);
+  }
+  __syncthreads();
+  if (x.j >= g.nv) return;
+  const Vel v = velocity_of(g, x.j);
+#pragma unroll 4
+  for (int i = 0; i < kXNodes; ++i) {
+    const int64_t n = x.n + i;
+    if (n >= g.nx) break;
+    const double* q = prim + n * 5;
+    const double dx = v.u[0] - q[1], dy = v.u[1] - q[2], dz = v.u[2] - q[3];
+    const int64_t e = n / g.ns;
+    f[f_offset(g, e, (int)(n - e * g.ns), x.j)] =
+        (ST)(nrm[i] * exp(-(dx * dx + dy * dy + dz * dz) / (2.0 * q[4])));
   }
 }
 
@@ -918,37 +964,48 @@ hipError_t launch_reduce_partials(const DevGeom& g, const double* partials, doub
   return hipGetLastError();
 }
 
+// Work-groups of an exchange kernel that covers the nodes of entries i0 ..
+// i0 + m - 1 (from node n0 on).
+static unsigned exchange_grid(const DevGeom& g, int64_t i0, int64_t m, int64_t* n0) {
+  *n0 = i0 / g.nv;
+  const int64_t nodes = (i0 + m - 1) / g.nv + 1 - *n0;
+  return (unsigned)((nodes + kXNodes - 1) / kXNodes * ((g.nv + kBlock - 1) / kBlock));
+}
+
 hipError_t launch_maxwellian(int precision, const DevGeom& g, const double* prim, void* f,
                              hipStream_t s) {
-  const dim3 grid((unsigned)std::min<int64_t>(g.nx * g.nchunk, 1 << 20));
+  int64_t n0 = 0;
+  const dim3 grid(exchange_grid(g, 0, g.nx * g.nv, &n0)), block(kBlock);
   if (precision == 0)
-    hipLaunchKernelGGL(k_maxwellian<double>, grid, dim3(kBlock), 0, s, g, prim, (double*)f);
+    hipLaunchKernelGGL(k_maxwellian<double>, grid, block, 0, s, g, prim, (double*)f);
   else
-    hipLaunchKernelGGL(k_maxwellian<float>, grid, dim3(kBlock), 0, s, g, prim, (float*)f);
+    hipLaunchKernelGGL(k_maxwellian<float>, grid, block, 0, s, g, prim, (float*)f);
   return hipGetLastError();
 }
 
 hipError_t launch_to_storage(int precision, const DevGeom& g, const double* in, void* out,
                              int64_t i0, int64_t m, hipStream_t s) {
   if (m <= 0) return hipSuccess;
-  const unsigned grid = (unsigned)std::min<int64_t>(grid_of(m, 256), 65536);
+  int64_t n0 = 0;
+  const dim3 grid(exchange_grid(g, i0, m, &n0)), block(kBlock);
   if (precision == 0)
-    hipLaunchKernelGGL(k_to_internal<double>, dim3(grid), dim3(256), 0, s, g, in, (double*)out, i0, m);
+    hipLaunchKernelGGL(k_to_internal<double>, grid, block, 0, s, g, in, (double*)out, i0, m, n0);
   else
-    hipLaunchKernelGGL(k_to_internal<float>, dim3(grid), dim3(256), 0, s, g, in, (float*)out, i0, m);
+    hipLaunchKernelGGL(k_to_internal<float>, grid, block, 0, s, g, in, (float*)out, i0, m, n0);
   return hipGetLastError();
 }
 
 hipError_t launch_from_storage(int precision, const DevGeom& g, const void* in, double* out,
                                int64_t i0, int64_t m, hipStream_t s) {
   if (m <= 0) return hipSuccess;
-  const unsigned grid = (unsigned)std::min<int64_t>(grid_of(m, 256), 65536);
+  int64_t n0 = 0;
+  const dim3 grid(exchange_grid(g, i0, m, &n0)), block(kBlock);
   if (precision == 0)
-    hipLaunchKernelGGL(k_to_canonical<double>, dim3(grid), dim3(256), 0, s, g, (const double*)in,
-                       out, i0, m);
+    hipLaunchKernelGGL(k_to_canonical<double>, grid, block, 0, s, g, (const double*)in, out, i0, m,
+                       n0);
   else
-    hipLaunchKernelGGL(k_to_canonical<float>, dim3(grid), dim3(256), 0, s, g, (const float*)in,
-                       out, i0, m);
+    hipLaunchKernelGGL(k_to_canonical<float>, grid, block, 0, s, g, (const float*)in, out, i0, m,
+                       n0);
   return hipGetLastError();
 }
 
