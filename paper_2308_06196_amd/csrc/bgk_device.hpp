@@ -690,6 +690,30 @@ __device__ __forceinline__ void element_partials_mfma(const CT (&fv)[NS], const 
   }
 }
 
+// Limiter counters of a work-group: every wave puts its counts of contracted
+// slices and of non-positive means in LDS, and one lane adds them up behind a
+// barrier, so that a work-group makes at most one atomic per counter (one per
+// wave and element on one address took some 8 ns each).
+struct LimiterCounts {
+  int hits[kBlock / 64], bad[kBlock / 64];
+};
+__device__ __forceinline__ void limiter_count(LimiterCounts& c, int hits, int bad, const int tid) {
+  if ((tid & 63) == 0) {
+    c.hits[tid >> 6] = hits;
+    c.bad[tid >> 6] = bad;
+  }
+}
+__device__ __forceinline__ void limiter_add(const LimiterCounts& c, unsigned long long* diag,
+                                            const int tid) {
+  if (tid == 0) {
+    int h = 0, b = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) h += c.hits[w], b += c.bad[w];
+    if (h) atomicAdd(&diag[2], (unsigned long long)h);
+    if (b) atomicAdd(&diag[3], (unsigned long long)b);
+  }
+}
+
 // BGK collision term at one (node, velocity) in FP64 (Sec. 2, C = (g - f)/tau;
 // Sec. 2.1, g the discretely conservative equilibrium): from the node's FP64
 // equilibrium row ti (Ex with exp(alpha_0) and 1/tau folded in, Ey, Ez, then
@@ -903,6 +927,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   __shared__ FaceRows<CT> frows[kBlock / 64];
   __shared__ LineOps lops[kMfma ? kBlock / 64 : 1];
   __shared__ CT trl[kTrLds ? NT * kBlock : 1];  // carried traces, [line][lane]
+  __shared__ LimiterCounts lim;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   double* tab = reinterpret_cast<double*>(dyn_lds);
 
@@ -1325,12 +1350,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
 #pragma unroll
         for (int i = 0; i < NS; ++i) o[i] = mean + beta * (o[i] - mean);
       }
-      const unsigned long long nh = __popcll(__ballot(hit));
-      const unsigned long long nb = __popcll(__ballot(hit && !(mean > (CT)0)));
-      if ((tid & 63) == 0 && nh) {
-        atomicAdd(&A.diag[2], nh);
-        if (nb) atomicAdd(&A.diag[3], nb);
-      }
+      limiter_count(lim, __popcll(__ballot(hit)), __popcll(__ballot(hit && !(mean > (CT)0))), tid);
     }
     if constexpr (INC) {
       // the increment o - F in BF16, and the stored state F + increment for
@@ -1388,6 +1408,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
     // with them
     if (A.collide) lds_barrier();
     element_partials_mfma<NS, ST, CT>(o, vel, A.partials, node0, g.nx, chunk, dyn_lds, red, tid);
+    if (A.limiter) limiter_add(lim, A.diag, tid);  // (behind the partials' barrier)
     if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
   }
 }

@@ -292,6 +292,7 @@ __device__ __forceinline__ void hex_walk(table_ptr<StageArgs> ap, const int chun
 #pragma unroll
   for (int l = 0; l < N1; ++l) trx[l] = (CT)0;
 
+  int hits = 0, bad = 0;  // limiter counters of the wave over the walk
   for (int ix = 0, iy = 0; iy < nyt;) {
     asm volatile("" : "+s"(ap));
     const int64_t eoff = e * estride + own_off;
@@ -517,12 +518,8 @@ __device__ __forceinline__ void hex_walk(table_ptr<StageArgs> ap, const int chun
 #pragma unroll
         for (int q = 0; q < P2; ++q) o[q] = mean + beta * (o[q] - mean);
       }
-      const unsigned long long nh = __popcll(__ballot(hit && az == 0));
-      const unsigned long long nbad = __popcll(__ballot(hit && az == 0 && !(mean > (CT)0)));
-      if (lane == 0 && nh) {
-        atomicAdd(&A.diag[2], nh);
-        if (nbad) atomicAdd(&A.diag[3], nbad);
-      }
+      hits += __popcll(__ballot(hit && az == 0));
+      bad += __popcll(__ballot(hit && az == 0 && !(mean > (CT)0)));
     }
     if (INC && !A.out_full) {
       if constexpr (INC) {
@@ -608,6 +605,10 @@ __device__ __forceinline__ void hex_walk(table_ptr<StageArgs> ap, const int chun
     e = e_next;
     ix = jx;
     iy = jy;
+  }
+  if (lane == 0) {
+    if (hits) atomicAdd(&args().diag[2], (unsigned long long)hits);
+    if (bad) atomicAdd(&args().diag[3], (unsigned long long)bad);
   }
   if (tid == 0 && count) atomicAdd(&args().diag[4], 1ull);
 }

@@ -22,55 +22,30 @@ namespace bgk {
 // three velocity components, so every sum over the N_v nodes factorises into
 // one-dimensional sums S_c^n = sum_b w_c[b] E_c[b] u_b^n (n = 0..4) with
 // E_c[b] = exp(alpha_{1+c} u_b + alpha_4 u_b^2 / 2): O(3 N_1d) work per node.
+//
+// The same product form makes the Newton system an arrow: with m_c^n = S_c^n /
+// S_c^0 and A = exp(alpha_0) S_x^0 S_y^0 S_z^0, the Jacobian is A times the
+// second moments of psi under g; less the mass row, it is their covariance,
+// in which the velocity components are independent. With f = F / A, M = sum_c
+// m_c^2 / 2, variances s_c = m_c^2 - (m_c^1)^2, covariances c_c = (m_c^3 - m_c^1
+// m_c^2) / 2 with the energy, V = sum_c (m_c^4 - (m_c^2)^2) / 4, and the reduced
+// right-hand sides r_c = f_c - m_c^1 f_0, r_4 = f_4 - M f_0:
+//   d_4 = (r_4 - sum_c c_c r_c / s_c) / (V - sum_c c_c^2 / s_c),
+//   d_c = (r_c - c_c d_4) / s_c,   d_0 = f_0 - sum_c m_c^1 d_c - M d_4.
+// (An indefinite pivot marks the node failed.) The solve is bound by its chain
+// of dependent FP64 operations on small meshes and by FP64 issue on large ones;
+// a 5 x 5 Cholesky factorisation in its place, with five square roots and five
+// more divisions in the chain, took 1.6 us longer a launch on 96 nodes (13.1
+// against 11.5) and 8.5 on 216,000 (167.6 against 159.0).
 // ---------------------------------------------------------------------------
-__device__ static int chol5_solve(double J[5][5], const double* b, double* x) {
-  double L[5][5], R[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int k = 0; k < 5; ++k) L[i][k] = 0.0;
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-#pragma unroll
-    for (int k = 0; k <= i; ++k) {
-      double s = J[i][k];
-#pragma unroll
-      for (int m = 0; m < k; ++m) s -= L[i][m] * L[k][m];
-      if (i == k) {
-        if (!(s > 0.0)) return 1;
-        L[i][i] = sqrt(s);
-        R[i] = 1.0 / L[i][i];
-      } else {
-        L[i][k] = s * R[k];
-      }
-    }
-  }
-  double y[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    double s = b[i];
-#pragma unroll
-    for (int m = 0; m < i; ++m) s -= L[i][m] * y[m];
-    y[i] = s * R[i];
-  }
-#pragma unroll
-  for (int i = 4; i >= 0; --i) {
-    double s = y[i];
-#pragma unroll
-    for (int m = i + 1; m < 5; ++m) s -= L[m][i] * x[m];
-    x[i] = s * R[i];
-  }
-  return 0;
-}
-
 // All-reduce of one FP64 value over the T lanes of a team (T = 16: one DPP
 // row, partners lane ^ 8, the mirror inside 8 lanes, lane ^ 2, lane ^ 1;
-// T = 8 from the mirror on; T = 4: one quad; T = 2: a lane pair). Each step
+// T = 4: one quad; T = 2: a lane pair). Each step
 // pairs lanes symmetrically, so every lane ends with the same bits.
 template <int T>
 __device__ __forceinline__ double team_sum(double x) {
   if constexpr (T == 16) x += dpp_partner<8>(x);
-  if constexpr (T >= 8) x += dpp_partner<4>(x);
+  if constexpr (T == 16) x += dpp_partner<4>(x);
   if constexpr (T >= 4) x += dpp_partner<2>(x);
   x += dpp_partner<1>(x);
   return x;
@@ -89,21 +64,29 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
   // every lane reaches the wave-level counter reduction at the end
   const bool active = node_raw < g.nx;
   const int64_t node = active ? node_raw : g.nx - 1;
+  const unsigned long long seen =
+      __hip_atomic_load(&A.diag[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   double Q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const double* pp = A.partials + node * 5;  // chunk c at pp[c * nx * 5]
-  // chunk partials: batches of 4 chunks per lane, all loads of a batch in flight
-  for (int c0 = 0; c0 < g.nchunk; c0 += 4 * kTeam) {
-    double v[4][5];
+  constexpr int kH = kTeam >= 16 ? 1 : 2;
+  const int nmax = max(g.nv1[0], max(g.nv1[1], g.nv1[2]));
+  // chunk partials: batches of kPB chunks per lane, all loads of a batch in
+  // flight (chunks past the last read that one again, with weight 0: a
+  // conditional load becomes a branch of its own)
+  constexpr int kPB = kTeam >= 16 ? 2 : 8;
+  const int64_t pstride = g.nx * 5;
+  for (int c0 = r; c0 < g.nchunk; c0 += kPB * kTeam) {
+    double v[kPB][5];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = c0 + u * kTeam + r;
+    for (int u = 0; u < kPB; ++u) {
+      const double* p = pp + (int64_t)min(c0 + u * kTeam, g.nchunk - 1) * pstride;
 #pragma unroll
-      for (int m = 0; m < 5; ++m) v[u][m] = c < g.nchunk ? pp[(int64_t)c * g.nx * 5 + m] : 0.0;
+      for (int m = 0; m < 5; ++m) v[u][m] = p[m];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < kPB; ++u)
 #pragma unroll
-      for (int m = 0; m < 5; ++m) Q[m] += v[u][m];
+      for (int m = 0; m < 5; ++m) Q[m] += c0 + u * kTeam < g.nchunk ? v[u][m] : 0.0;
   }
 #pragma unroll
   for (int m = 0; m < 5; ++m) Q[m] = team_sum<kTeam>(Q[m]);
@@ -135,30 +118,38 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
     al[3] = Q[3] / rho / th;
     al[4] = -1.0 / th;
     const double sq = rho * sqrt(th);
-    const double sc[5] = {rho, sq, sq, sq, Q[4]};
+    const double isq = 1.0 / sq;
+    const double isc[5] = {1.0 / rho, isq, isq, isq, 1.0 / Q[4]};
     // the non-conservative model keeps the continuous Maxwellian (no solve)
     for (int it = 0; !A.continuous; ++it) {
+      // the three components together (and two nodes each where a lane has
+      // several): independent exponentials, whose latency bounds the sums
       double S[3][5];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int n = 0; n < 5; ++n) S[c][n] = 0.0;
-        const int N = g.nv1[c];
-        for (int b = r; b < N; b += kTeam) {
-          const double u = g.vlo[c] + b * g.du[c];
-          double wc = g.du[c];
-          if (b == 0 || b == N - 1) wc *= 0.5;
-          const double t = wc * exp(al[1 + c] * u + al[4] * (0.5 * u * u));
-          const double u2 = u * u;
-          S[c][0] += t;
-          S[c][1] += t * u;
-          S[c][2] += t * u2;
-          S[c][3] += t * u2 * u;
-          S[c][4] += t * u2 * u2;
+      for (int b0 = r; b0 < nmax; b0 += kH * kTeam) {
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const int b = b0 + h * kTeam, N = g.nv1[c], bb = b < N ? b : N - 1;
+            const double u = g.vlo[c] + bb * g.du[c], u2 = u * u;
+            const double wc = b >= N ? 0.0 : g.du[c] * (bb == 0 || bb == N - 1 ? 0.5 : 1.0);
+            const double t = wc * exp(al[1 + c] * u + al[4] * (0.5 * u2));
+            S[c][0] += t;
+            S[c][1] += t * u;
+            S[c][2] += t * u2;
+            S[c][3] += t * u2 * u;
+            S[c][4] += t * u2 * u2;
+          }
         }
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int n = 0; n < 5; ++n) S[c][n] = team_sum<kTeam>(S[c][n]);
-      }
       double m[3][5];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -168,36 +159,13 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
         for (int n = 1; n < 5; ++n) m[c][n] = S[c][n] * inv;
       }
       const double A0 = exp(al[0]) * S[0][0] * S[1][0] * S[2][0];
-      double G[5], J[5][5];
-      G[0] = A0;
-      G[1] = A0 * m[0][1];
-      G[2] = A0 * m[1][1];
-      G[3] = A0 * m[2][1];
-      G[4] = A0 * 0.5 * (m[0][2] + m[1][2] + m[2][2]);
-#pragma unroll
-      for (int a = 0; a < 5; ++a) {
-        J[0][a] = G[a];
-        J[a][0] = G[a];
-      }
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-#pragma unroll
-        for (int c2 = 0; c2 < 3; ++c2)
-          J[1 + c][1 + c2] = (c == c2) ? A0 * m[c][2] : A0 * m[c][1] * m[c2][1];
-        double t = m[c][3];
-#pragma unroll
-        for (int c2 = 0; c2 < 3; ++c2)
-          if (c2 != c) t += m[c][1] * m[c2][2];
-        J[1 + c][4] = J[4][1 + c] = A0 * 0.5 * t;
-      }
-      J[4][4] = A0 * 0.25 *
-                (m[0][4] + m[1][4] + m[2][4] +
-                 2.0 * (m[0][2] * m[1][2] + m[0][2] * m[2][2] + m[1][2] * m[2][2]));
+      const double M = 0.5 * (m[0][2] + m[1][2] + m[2][2]);
+      const double G[5] = {A0, A0 * m[0][1], A0 * m[1][1], A0 * m[2][1], A0 * M};
       double F[5], res = 0.0;
 #pragma unroll
       for (int a = 0; a < 5; ++a) {
         F[a] = G[a] - Q[a];
-        const double ra = fabs(F[a]) / sc[a];
+        const double ra = fabs(F[a]) * isc[a];
         if (!(ra <= res)) res = ra;
       }
       iters = it + 1;
@@ -206,10 +174,36 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
         status = 1;
         break;
       }
-      double d[5];
-      if (chol5_solve(J, F, d)) {
+      const double iA = 1.0 / A0;
+      double f[5];
+#pragma unroll
+      for (int a = 0; a < 5; ++a) f[a] = F[a] * iA;
+      double d[5], is[3], cv[3], r[3];
+      double r4 = f[4] - M * f[0], V = 0.0;
+      bool spd = A0 > 0.0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double var = m[c][2] - m[c][1] * m[c][1];
+        spd = spd && var > 0.0;
+        is[c] = 1.0 / var;
+        cv[c] = 0.5 * (m[c][3] - m[c][1] * m[c][2]);
+        r[c] = f[1 + c] - m[c][1] * f[0];
+        V += 0.25 * (m[c][4] - m[c][2] * m[c][2]) - cv[c] * cv[c] * is[c];
+        r4 -= cv[c] * r[c] * is[c];
+      }
+      // (an energy pivot of rounding size: the energy moment is a multiple of
+      // the mass, as with two velocity nodes per component)
+      const double e4 = 0.25 * (m[0][4] + m[1][4] + m[2][4]);
+      if (!(spd && V > 64.0 * 0x1p-53 * e4)) {
         status = 2;
         break;
+      }
+      d[4] = r4 / V;
+      d[0] = f[0] - M * d[4];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        d[1 + c] = (r[c] - cv[c] * d[4]) * is[c];
+        d[0] -= m[c][1] * d[1 + c];
       }
       double an[5];
 #pragma unroll
@@ -238,25 +232,25 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
   const double tr = th / A.theta_ref;
   const double mu = A.sutherland > 0.0
                         ? A.mu_ref * tr * sqrt(tr) * (A.theta_ref + A.sutherland) / (th + A.sutherland)
-                        : A.mu_ref * pow(tr, A.omega);
+                        : A.omega != 0.0 ? A.mu_ref * pow(tr, A.omega)
+                                         : A.mu_ref;
   const double itau = P / mu;  // 1 / tau
   // one-dimensional factors of the equilibrium in FP64 for every storage
   // precision: exp(alpha_0) and 1/tau folded into x, so that the stage kernels
   // form the collision term as Ex[bx] Ey[by] Ez[bz] - f / tau
   double* row = (double*)A.etab + node * g.tabw;
-  int off = 0;
+  const int off1 = g.nv1[0], off2 = off1 + g.nv1[1], off = off2 + g.nv1[2];
+  for (int b0 = r; b0 < nmax; b0 += kH * kTeam) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const int N = g.nv1[c];
-    const double a0 = c == 0 ? al[0] : 0.0;
-    if (active) {
-      for (int b = r; b < N; b += kTeam) {
+    for (int h = 0; h < kH; ++h) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const int b = b0 + h * kTeam;
         const double u = g.vlo[c] + b * g.du[c];
-        const double v = exp(a0 + al[1 + c] * u + al[4] * (0.5 * u * u));
-        row[off + b] = c == 0 ? v * itau : v;
+        const double v = exp((c == 0 ? al[0] : 0.0) + al[1 + c] * u + al[4] * (0.5 * u * u));
+        if (active && b < g.nv1[c]) row[(c == 0 ? 0 : c == 1 ? off1 : off2) + b] = c == 0 ? v * itau : v;
       }
     }
-    off += N;
   }
   if (r == 0 && active) {
 #pragma unroll
@@ -266,12 +260,16 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
     out[7] = (double)status;
     row[off] = itau;  // 1/tau closes the node's row
   }
-  // counters: one atomic per wave (the four teams of a wave reduced first)
+  // counters: at most one atomic per wave (its teams reduced first). The most
+  // iterations rise only in the first launches after a state is installed:
+  // waves that do not exceed the value seen at the start leave it alone. (One
+  // atomic per wave on one address cost more than the solve: 16,384 nodes with
+  // 4, 8, 16 lanes each 34.7, 41.6, 63.3 us, without them 25.6, 28.0, 34.5.)
   int itw = active ? iters : 0;
   for (int o = kTeam; o < 64; o <<= 1) itw = max(itw, __shfl_xor(itw, o, 64));
   const unsigned long long nfail = __popcll(__ballot(active && r == 0 && status != 0));
   if ((threadIdx.x & 63) == 0) {
-    if (itw > 0) atomicMax(&A.diag[0], (unsigned long long)itw);
+    if ((unsigned long long)itw > seen) atomicMax(&A.diag[0], (unsigned long long)itw);
     if (nfail) atomicAdd(&A.diag[1], nfail);
   }
 }
@@ -847,9 +845,10 @@ hipError_t launch_wall(int precision, bool canonical, const WallArgs& W, hipStre
 
 hipError_t launch_newton(const NewtonArgs& A, hipStream_t s) {
   // teams of 4 lanes per node once there are enough nodes to fill the GPU
-  // (measured on 16,384 nodes: 0.045 ms against 0.076 ms with 16 lanes and
-  // 0.047 ms with 2), of 2 lanes on large meshes (262,144 nodes: 0.146 ms
-  // against 0.240 ms with 4; 884,736 nodes: 0.54 ms against 0.72 ms)
+  // (16,384 nodes on 24^3 velocities: 26 us against 34 with 16 lanes or 2; 1948
+  // nodes on 22 x 23 x 21: 19 against 14.5 with 16), of 2 lanes on large meshes
+  // (262,144 nodes on 16^3: 108 us against 124 with 4 and 280 with 16; 216,000
+  // nodes on 20^3: 145 against 154)
   const int team = newton_team(A.g.nx);
   if (team == 2)
     hipLaunchKernelGGL(k_newton<2>, dim3(grid_of(A.g.nx * 2, 256)), dim3(256), 0, s, A);

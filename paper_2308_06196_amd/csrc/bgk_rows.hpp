@@ -45,6 +45,7 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
   constexpr int NL = ipow(N1, DIM - 1);  // lines per element and axis
   constexpr int R = E * NS;
   __shared__ double red[(kBlock / 64) * part_rows<R>() * 5];
+  __shared__ LimiterCounts lim;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   double* tab = reinterpret_cast<double*>(dyn_lds);
 
@@ -327,6 +328,7 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
 #pragma unroll
     for (int q = 0; q < R; ++q) o[q] = MODE == 0 ? ca * fnv[q] + acc[q] : acc[q];
     if (A.limiter) {
+      int hits = 0, bad = 0;
 #pragma unroll
       for (int i = 0; i < E; ++i) {
         CT(&oi)[NS] = *reinterpret_cast<CT(*)[NS]>(&o[i * NS]);
@@ -341,13 +343,10 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
 #pragma unroll
           for (int q = 0; q < NS; ++q) oi[q] = mean + beta * (oi[q] - mean);
         }
-        const unsigned long long nh = __popcll(__ballot(hit));
-        const unsigned long long nb = __popcll(__ballot(hit && !(mean > (CT)0)));
-        if ((tid & 63) == 0 && nh) {
-          atomicAdd(&A.diag[2], nh);
-          if (nb) atomicAdd(&A.diag[3], nb);
-        }
+        hits += __popcll(__ballot(hit));
+        bad += __popcll(__ballot(hit && !(mean > (CT)0)));
       }
+      limiter_count(lim, hits, bad, tid);
     }
     if (INC && !A.out_full) {
       if constexpr (INC) {
@@ -398,6 +397,7 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
     if (A.collide) lds_barrier();
     element_partials_mfma<R, ST, CT>(o, vel, A.partials, node0, g.nx, chunk, dyn_lds, red, tid,
                                      cnt * NS);
+    if (A.limiter) limiter_add(lim, A.diag, tid);  // (behind the partials' barrier)
     if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
   }
 }
