@@ -145,8 +145,9 @@ struct StageArgs {
   int32_t sweep_seg;  // column sweeps: elements per work item along the last axis
   int32_t xcd_part;   // XCDs per chunk group of xcd_chunk_remap (else xcd_remap)
   int32_t rows;  // 1: the RK stages run several elements per work-group (k_stage_rows)
-  // hexahedral walk (k_stage_walk): elements per tile row, rows per tile, most
-  // row entries per node of any velocity chunk
+  // walks: elements per tile row and rows per tile (k_stage_walk), elements per
+  // run (k_stage_xwalk: walk_tx, walk_ty 0), most row entries per node of any
+  // velocity chunk
   int32_t walk_tx, walk_ty, walk_ncols;
 };
 

@@ -808,6 +808,7 @@ int velocities_per_block(int dim, int order, int precision) {
 hipError_t launch_stage(int precision, int mode, const StageArgs& A, hipStream_t s) {
   if (A.ecount <= 0) return hipSuccess;
   if (mode == 0 && A.rows) return launch_rows(precision, A, s);
+  if (mode == 0 && A.walk_tx > 0 && A.walk_ty == 0) return launch_xwalk(precision, A, s);
   // BF16 storage (precision 2): FP32 state with BF16 stage increments; the
   // RK stages use the increment kernels, everything else the FP32 ones
   return precision == 0 ? stage_dispatch<double>(mode, false, A, s)

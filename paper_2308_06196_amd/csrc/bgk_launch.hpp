@@ -37,6 +37,10 @@ hipError_t launch_rows(int precision, const StageArgs& A, hipStream_t s);
 hipError_t launch_rows_batch(int precision, int dim, int order, int stage, const StageArgs* args,
                              const BatchList* list, size_t tab_bytes, unsigned grid,
                              hipStream_t s);
+// Some p = 3 quadrilaterals and p <= 2 hexahedra: RK stage by runs of elements
+// along x (k_stage_xwalk), and their length (0: not used).
+hipError_t launch_xwalk(int precision, const StageArgs& A, hipStream_t s);
+int xwalk_length(const DevGeom& g, int precision);
 // mode 0: fused RK stage (a variant that does not read f^n when a = 0);
 // 1: residual L(f) in FP64; 2: moment partials only; 3, 4: the same two of a
 // canonical FP64 array A.fin in lexicographic velocity order (A.g with a single

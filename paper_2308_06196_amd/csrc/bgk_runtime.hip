@@ -18,7 +18,6 @@
 #include <vector>
 
 #include "../../include/bgk.h"
-#include "bgk_hexwalk.hpp"
 #include "bgk_launch.hpp"
 
 using namespace bgk;
@@ -738,26 +737,27 @@ void init_solver(bgk_solver* s, const bgk_problem* pb, char* ws, hipStream_t str
       s->rcols_host[c] = row_cols(g, c * vb, (int)std::min<int64_t>((int64_t)(c + 1) * vb, g.nv));
   }
   setup_walls(s);
-  if (brick && pb->dim == 3 && !hex_one_lane(pb->order, pb->precision)) {
-    // the chunk whose rows take the most LDS
-    for (const RowCols& r : s->rcols_host)
-      if (!s->walk_ncols || HexWalk::rows_bytes(r.ncols) > HexWalk::rows_bytes(s->walk_ncols))
-        s->walk_ncols = r.ncols;
-    walk_tile(g, pb->precision, s->walk_ncols, &s->walk_tx, &s->walk_ty);
+  if (brick) {
+    // walks: the chunk whose rows take the most LDS, then the tile or run
+    for (const RowCols& r : s->rcols_host) s->walk_ncols = std::max(s->walk_ncols, r.ncols);
+    if (pb->dim == 3 && !hex_one_lane(pb->order, pb->precision))
+      walk_tile(g, pb->precision, s->walk_ncols, &s->walk_tx, &s->walk_ty);
+    else if (s->L.wall_points == 0)
+      s->walk_tx = xwalk_length(g, pb->precision);
   }
   if (brick) s->rows = rows_pay(g, pb->mu_ref > 0.0);
-  if (brick) s->sweep_seg = sweep_segment(g, pb->precision, pb->mu_ref > 0.0);
+  if (brick && !s->walk_tx) s->sweep_seg = sweep_segment(g, pb->precision, pb->mu_ref > 0.0);
   if (brick) {
     // XCDs sharing a velocity chunk in the stage launches (xcd_chunk_remap):
     // all eight for column sweeps (tgv3d FP32 3.15 against 3.25 ms per
-    // launch, box2d FP64 1 % faster), four for the plane-split hexahedra (all
-    // z-layers of one tile column then sit on one XCD at 16 layers);
-    // contiguous ranges for
-    // the per-element one-lane kernels (the Mach-2 box 2 % slower with eight).
+    // launch, box2d FP64 1 % faster) and x walks, four for the plane-split
+    // hexahedra (all z-layers of one tile column then sit on one XCD at 16
+    // layers); contiguous ranges for the per-element one-lane kernels (the
+    // Mach-2 box 2 % slower with eight).
     // BGK_XCD_PART overrides the choice (0: contiguous ranges).
     const char* env = getenv("BGK_XCD_PART");
     s->xcd_part = env                                            ? atoi(env)
-                  : s->sweep_seg > 0                             ? 8
+                  : s->sweep_seg > 0 || (s->walk_tx > 0 && s->walk_ty == 0) ? 8
                   : pb->dim == 3 && !hex_one_lane(pb->order, pb->precision) ? 4
                                                                  : 0;
   }
