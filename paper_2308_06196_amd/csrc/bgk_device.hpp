@@ -456,7 +456,7 @@ template <> struct Compute<double> { using T = double; };
 template <> struct Compute<float> { using T = float; };
 
 // sum_i W_i v_i over the (p+1)^D nodes of a D-dimensional tensor block
-// (D = 1, 2), W_i the product of the 1-D Gauss weights of node i, summed one
+// (D = 1, 2, 3), W_i the product of the 1-D Gauss weights of node i, summed one
 // dimension at a time.
 template <int D, int N1, typename CT>
 __device__ __forceinline__ CT tensor_wsum(const CT* v, const CT* w) {
@@ -468,7 +468,7 @@ __device__ __forceinline__ CT tensor_wsum(const CT* v, const CT* w) {
   } else {
     CT s = (CT)0;
 #pragma unroll
-    for (int b = 0; b < N1; ++b) s += sreg(w[b]) * tensor_wsum<D - 1, N1>(v + b * N1, w);
+    for (int b = 0; b < N1; ++b) s += sreg(w[b]) * tensor_wsum<D - 1, N1>(v + b * ipow(N1, D - 1), w);
     return s;
   }
 }
