@@ -29,14 +29,14 @@ namespace bgk {
 //
 // Used where it measured faster than one work-group per element (ms per stage
 // launch, per element / walk): p = 3 quadrilaterals in FP32 (32^2 box on 24^3
-// velocities 0.587 / 0.541, 45 x 29 box on 21 x 22 x 17 0.432 / 0.419); p = 1
-// hexahedra (16^3 elements on 16^3, FP64 0.827 / 0.726, FP32 0.527 / 0.463, BF16
-// increments 0.529 / 0.460); p = 2 hexahedra with increments (20^3 elements on
+// velocities 0.587 / 0.541, 45 x 29 box on 21 x 22 x 17 0.432 / 0.419) and with
+// increments (0.585 / 0.521, 0.428 / 0.406: three waves per SIMD, as with four the
+// walk spills and takes 0.635); p = 1 hexahedra (16^3 elements on 16^3, FP64 0.827 /
+// 0.726, FP32 0.527 / 0.463, BF16 increments 0.529 / 0.460); p = 2 hexahedra with increments (20^3 elements on
 // 20^3 9.72 / 5.85: the element and its increments need more registers than
 // the per-element kernel's four waves per SIMD leave). Not for p = 3
-// quadrilaterals in FP64 (1.04 / 1.25) and with increments (0.585 / 0.635) and
-// p = 2 hexahedra in FP64 (20^3 velocities, 14^3 elements 3.29 / 3.88) and FP32
-// (4.81 / 5.2), whose loop spills or runs at fewer waves.
+// quadrilaterals in FP64 (1.04 / 1.25) and p = 2 hexahedra in FP64 (20^3
+// velocities, 14^3 elements 3.29 / 3.88) and FP32 (4.81 / 5.2), whose loop spills or runs at fewer waves.
 template <int DIM, int P>
 struct XWalk {
   static constexpr int N1 = P + 1, NS = ipow(N1, DIM), NL = ipow(N1, DIM - 1);
@@ -50,9 +50,9 @@ struct XWalk {
 };
 
 // Waves per SIMD: what the registers of a variant allow without spills.
-template <int DIM, int P, typename ST>
+template <int DIM, int P, typename ST, bool INC>
 constexpr int xwalk_waves() {
-  return DIM == 3 && P == 2 ? 2 : sizeof(ST) == 8 ? 3 : 4;
+  return DIM == 3 && P == 2 ? 2 : sizeof(ST) == 8 || (DIM == 2 && INC) ? 3 : 4;
 }
 
 template <int DIM, int P, typename ST, int MODE, bool INC>
@@ -429,7 +429,7 @@ __device__ __forceinline__ void xwalk(table_ptr<StageArgs> ap, const int chunk, 
 
 template <int DIM, int P, typename ST, int MODE, bool INC = false>
 __global__ void __launch_bounds__(kBlock)
-    __attribute__((amdgpu_waves_per_eu(xwalk_waves<DIM, P, ST>())))
+    __attribute__((amdgpu_waves_per_eu(xwalk_waves<DIM, P, ST, INC>())))
     k_stage_xwalk(const StageArgs A) {
   const DevGeom& g = A.g;
   const int len = A.walk_tx, nx = g.nelem[0];

@@ -1,7 +1,7 @@
 """Stage kernel that walks runs of elements along x (one lane per velocity).
 
-p = 3 quadrilaterals in FP32, p = 1 hexahedra in every precision and p = 2
-hexahedra with BF16 increments walk once the mesh is large enough; BGK_XWALK
+p = 3 quadrilaterals in FP32 and with BF16 increments, p = 1 hexahedra in every
+precision and p = 2 hexahedra with BF16 increments walk once the mesh is large enough; BGK_XWALK
 (read when a solver is created) forces the run length (0: one work-group per
 element). The sums and their order are those of the per-element kernels, so
 every length must give their bits and counters: runs of one element, lengths
@@ -21,7 +21,7 @@ from tests.helpers import initial_state, oracle_problem
 
 pytestmark = pytest.mark.gpu
 
-FAMILIES = [(2, 3, 1), (3, 1, 0), (3, 1, 1), (3, 1, 2), (3, 2, 2)]
+FAMILIES = [(2, 3, 1), (2, 3, 2), (3, 1, 0), (3, 1, 1), (3, 1, 2), (3, 2, 2)]
 # nelem, nvel, walls, collisions, run lengths
 SHAPES = {
     "uniform": ((5, 3, 2), (8, 8, 8), 0, True, (1, 2, 3, 5)),
