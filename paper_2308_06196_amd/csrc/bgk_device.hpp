@@ -343,13 +343,21 @@ __host__ __device__ __forceinline__ int vel_slot_of_canonical(const DevGeom& g, 
 __host__ __device__ __forceinline__ void slot_nodes(const DevGeom& g, int j, int (&b)[3]) {
   // octant: the last one starting at or before j (empty octants start where
   // the next one does, so they are never picked)
-  int o = 0;
+  // (its first slot is selected with it: an indexed entry would be one more
+  // load, per lane, in the chain of latencies that every work-group starts with;
+  // p = 2 hexahedra in FP32, 20^3 elements on 20^3 velocities, 5.01 / 4.89 ms per
+  // stage, 27 x 31 p = 3 residual 600 / 578 us with the load / with the select)
+  int o = 0, first = 0;
 #pragma unroll
-  for (int q = 1; q < 8; ++q) o = j >= g.voct[q] ? q : o;
+  for (int q = 1; q < 8; ++q) {
+    const int s = g.voct[q];
+    o = j >= s ? q : o;
+    first = j >= s ? s : first;
+  }
   int n[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) n[k] = (o >> k) & 1 ? g.nv1[k] - g.vsplit[k] : g.vsplit[k];
-  const int loc = j - g.voct[o], r = loc / n[0], l2 = r / n[1];
+  const int loc = j - first, r = loc / n[0], l2 = r / n[1];
   const int l[3] = {loc - r * n[0], r - l2 * n[1], l2};
 #pragma unroll
   for (int k = 0; k < 3; ++k) b[k] = l[k] + ((o >> k) & 1 ? g.vsplit[k] : 0);
@@ -370,9 +378,6 @@ __device__ __forceinline__ Vel velocity_of(const DevGeom& g, int j) {
   return v;
 }
 
-// Uniform kernel-argument value as an opaque scalar register value: a
-// per-lane select between two of them then stays a register select (the
-// compiler would otherwise turn it into a load through a selected address).
 // Work-group barrier that orders LDS only. A plain __syncthreads() also
 // orders global memory, so it waits for every load and store in flight (the
 // bulk loads issued ahead of the table stores, the output stores ahead of the

@@ -358,9 +358,40 @@ __global__ void __launch_bounds__(kBlock) k_collision_moments(const StageArgs A,
 // net mass flux through the wall vanishes.
 // ---------------------------------------------------------------------------
 
+// Side of a wall work-group or flux point i: the last one that starts at or
+// before i, with its entries. All entries are read at once and selected: a loop
+// over the sides and indexed entries are a chain of scalar loads from the
+// argument memory, which is cold when a kernel starts.
+struct WallSide {
+  int k, side, off, blk0;
+};
+template <typename START>
+__device__ __forceinline__ WallSide wall_side(const WallArgs& W, const START& start, const int i) {
+  WallSide s[4];
+  int st[4], n = W.nside;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    s[q] = WallSide{W.side_k[q], W.side_s[q], W.off[q], W.blk0[q]};
+    st[q] = start[q];
+  }
+  // (the values, not the loads, are selected)
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    asm volatile("" : "+s"(s[q].k), "+s"(s[q].side), "+s"(s[q].off), "+s"(s[q].blk0), "+s"(st[q]));
+  WallSide r = s[0];
+#pragma unroll
+  for (int q = 1; q < 4; ++q)
+    if (q < n && i >= st[q]) r = s[q];
+  return r;
+}
+
 // One work-group = one wall-face element x one chunk of 256 velocities; the
 // flux points' partial sums are reduced in a fixed order (lanes by an xor
-// butterfly, then the four waves in LDS).
+// butterfly, then the four waves in LDS). Few work-groups with little work
+// each: bound by the chain of latencies in one of them (24 x 40 p = 2 channel on
+// 16^3 velocities, 768 work-groups: 19.3 us with eleven dependent scalar loads
+// and one vector load before the nodes', 5.4 with three). Waves without an
+// outgoing velocity load no nodes.
 template <int DIM, int P, typename ST, bool CAN = false>
 __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
   using Src = Source<CAN, ST>;
@@ -368,41 +399,49 @@ __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
   constexpr int NF = ipow(N1, DIM - 1);
   __shared__ double red[kBlock / 64][NF];
   const DevGeom& g = W.g;
-  int q = 0;
-  while (q + 1 < W.nside && b >= W.blk0[q + 1]) ++q;
-  const int k = W.side_k[q], side = W.side_s[q];
-  const int local = b - W.blk0[q];
+  const WallSide q = wall_side(W, W.blk0, b);
+  const bool along_y = DIM == 2 && q.k == 1;
+  const int local = b - q.blk0;
   const int face = local / g.nchunk, chunk = local % g.nchunk;
   // element: coordinate k on the wall, the other coordinate (2-D) = face
-  int ek[2] = {0, 0};
-  ek[k] = side == 0 ? 0 : g.nelem[k] - 1;
-  if (DIM == 2) ek[1 - k] = face;
-  const int64_t e = ek[0] + (int64_t)g.nelem[0] * ek[1];
+  const int nx = g.nelem[0], ny = g.nelem[1];
+  const int last = (along_y ? ny : nx) - 1, on = q.side == 0 ? 0 : last;
+  const int64_t e = DIM == 1 ? on : along_y ? face + (int64_t)nx * on : on + (int64_t)nx * face;
   const int64_t nv = g.nv;
   const int j = chunk * kBlock + (int)threadIdx.x;
   const bool valid = j < nv;
   const int jj = valid ? j : (int)nv - 1;
   const Vel vel = velocity_of(g, jj);
-  const double a = vel.u[k];
-  const bool outgoing = valid && (side == 0 ? a < 0.0 : a > 0.0);
+  const double a = along_y ? vel.u[1] : vel.u[0];
+  const bool outgoing = valid && (q.side == 0 ? a < 0.0 : a > 0.0);
   const double wt = outgoing ? vel.w * fabs(a) : 0.0;
-  const int S1 = k == 0 ? 1 : N1;
-  const typename Src::T* fe = (const typename Src::T*)W.fin + Src::offset(g, e, 0, jj);
-  const int64_t nst = Src::stride(g);
   double v[NF];
 #pragma unroll
-  for (int fp = 0; fp < NF; ++fp) {
-    const int base = (fp % S1) + (fp / S1) * S1 * N1;
-    double tr = 0.0;
+  for (int fp = 0; fp < NF; ++fp) v[fp] = 0.0;
+  if (__any(outgoing)) {
+    const typename Src::T* fe = (const typename Src::T*)W.fin + Src::offset(g, e, 0, jj);
+    // nodes of flux point fp's line: base(fp) + bb * along
+    const int64_t nst = Src::stride(g), along = along_y ? N1 * nst : nst,
+                  across = along_y ? nst : N1 * nst;
+    double lam[N1];
 #pragma unroll
-    for (int bb = 0; bb < N1; ++bb)
-      tr += (side == 0 ? W.lamL[bb] : W.lamR[bb]) * (double)(ST)fe[(base + bb * S1) * nst];
-    v[fp] = wt * tr;
-  }
+    for (int bb = 0; bb < N1; ++bb) {
+      const double l = W.lamL[bb], r = W.lamR[bb];
+      lam[bb] = q.side == 0 ? l : r;
+    }
 #pragma unroll
-  for (int fp = 0; fp < NF; ++fp) {
+    for (int fp = 0; fp < NF; ++fp) {
+      double tr = 0.0;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v[fp] += __shfl_xor(v[fp], o, 64);
+      for (int bb = 0; bb < N1; ++bb)
+        tr += lam[bb] * (double)(ST)fe[fp * across + bb * along];
+      v[fp] = wt * tr;
+    }
+#pragma unroll
+    for (int fp = 0; fp < NF; ++fp) {
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) v[fp] += __shfl_xor(v[fp], o, 64);
+    }
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) {
@@ -414,7 +453,7 @@ __device__ __forceinline__ void wall_flux_item(const WallArgs& W, const int b) {
     double sum = 0.0;
 #pragma unroll
     for (int w = 0; w < kBlock / 64; ++w) sum += red[w][threadIdx.x];
-    W.part[((int64_t)W.off[q] + face * NF + threadIdx.x) * g.nchunk + chunk] = sum;
+    W.part[((int64_t)q.off + face * NF + threadIdx.x) * g.nchunk + chunk] = sum;
   }
 }
 
@@ -436,12 +475,21 @@ __global__ void __launch_bounds__(kBlock) k_wall_flux_batch(table_ptr<WallArgs> 
 // inverse incoming flux of the side's unit wall Maxwellian.
 __device__ __forceinline__ void wall_rho_item(const WallArgs& W, const int t) {
   if (t >= W.npoints) return;
-  int q = 0;
-  while (q + 1 < W.nside && t >= W.off[q + 1]) ++q;
-  const double* p = W.part + (int64_t)t * W.g.nchunk;
+  const WallSide q = wall_side(W, W.off, t);
+  const int n = W.g.nchunk;
+  const double inv = W.wallp[(q.k * 2 + q.side) * 8 + 5];
+  const double* p = W.part + (int64_t)t * n;
   double sum = 0.0;
-  for (int c = 0; c < W.g.nchunk; ++c) sum += p[c];
-  W.rho[t] = sum * W.wallp[(W.side_k[q] * 2 + W.side_s[q]) * 8 + 5];
+  // (batches of loads in flight; those past the last chunk read it again)
+  constexpr int kB = 16;
+  for (int c0 = 0; c0 < n; c0 += kB) {
+    double v[kB];
+#pragma unroll
+    for (int u = 0; u < kB; ++u) v[u] = p[min(c0 + u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kB; ++u) sum += c0 + u < n ? v[u] : 0.0;
+  }
+  W.rho[t] = sum * inv;
 }
 
 __global__ void __launch_bounds__(256) k_wall_rho(const WallArgs W) {
