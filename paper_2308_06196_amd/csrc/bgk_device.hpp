@@ -1419,10 +1419,37 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   }
 }
 
+// Pointer into argument memory that is read-only while kernels run (kernel
+// arguments, descriptor tables): loads through the constant address space
+// become scalar loads that the compiler may repeat where a value is used,
+// instead of vector loads (or scalar registers) held across a loop.
+template <typename T>
+using table_ptr = const __attribute__((address_space(4))) T*;
+
+// One dword of every 64-byte line of the argument memory, read in one batch
+// at the kernel's start: the scalar loads that follow, each where its values
+// are first used, then find their lines in the scalar cache instead of waiting
+// for memory one after another. A launch that fills the GPU once or less is
+// bound by that chain (ten steps, us, without / with: 16 p = 1 line elements on
+// 8^3 velocities 592 / 567, 24 p = 3 in FP32 on 16^3 482 / 474, 6^2 p = 3 on 16^3
+// 813 / 795). Not where the kernel then spills or loses waves (with BF16 increments
+// 615 / 639; p = 2 hexahedra in FP32 4.9 / 7.9 ms a stage), nor in the equilibrium
+// solve, which gains nothing (476 / 477 on 32 p = 2 line elements).
+template <int LINES>
+__device__ __forceinline__ void warm_args() {
+  auto p = (table_ptr<int32_t>)__builtin_amdgcn_kernarg_segment_ptr();
+  int32_t v[LINES];
+#pragma unroll
+  for (int i = 0; i < LINES; ++i) v[i] = p[i * 16];
+#pragma unroll
+  for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(v[i]));
+}
+
 template <int DIM, int P, typename ST, int MODE, bool INC = false>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(stage_waves<DIM, P, typename Compute<ST>::T, INC>())))
     k_stage(const StageArgs A) {
+  if constexpr (DIM < 3 && !INC) warm_args<sizeof(StageArgs) / 64>();
   const int64_t w = xcd_chunk_remap(blockIdx.x, gridDim.x, A.ecount, A.xcd_part);
   typename Compute<ST>::T tr[sweep_tr_regs<DIM, P>()];
   stage_item<DIM, P, ST, MODE, INC>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount),
@@ -1446,12 +1473,6 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 
-// Pointer into argument memory that is read-only while kernels run (kernel
-// arguments, descriptor tables): loads through the constant address space
-// become scalar loads that the compiler may repeat where a value is used,
-// instead of vector loads (or scalar registers) held across a loop.
-template <typename T>
-using table_ptr = const __attribute__((address_space(4))) T*;
 template <typename T>
 __device__ __forceinline__ const T& table_entry(table_ptr<T> p, int64_t i) {
   return *(const T*)&p[i];
