@@ -340,13 +340,15 @@ __host__ __device__ __forceinline__ int vel_slot_of_canonical(const DevGeom& g, 
 }
 
 // Node indices b of slot j (the inverse of vel_slot).
+template <bool SELECT = true>
 __host__ __device__ __forceinline__ void slot_nodes(const DevGeom& g, int j, int (&b)[3]) {
   // octant: the last one starting at or before j (empty octants start where
   // the next one does, so they are never picked)
   // (its first slot is selected with it: an indexed entry would be one more
   // load, per lane, in the chain of latencies that every work-group starts with;
   // p = 2 hexahedra in FP32, 20^3 elements on 20^3 velocities, 5.01 / 4.89 ms per
-  // stage, 27 x 31 p = 3 residual 600 / 578 us with the load / with the select)
+  // stage, 27 x 31 p = 3 residual 600 / 578 us with the load / with the select;
+  // SELECT = false: the load, where the eight scalars cost spills)
   int o = 0, first = 0;
 #pragma unroll
   for (int q = 1; q < 8; ++q) {
@@ -357,15 +359,16 @@ __host__ __device__ __forceinline__ void slot_nodes(const DevGeom& g, int j, int
   int n[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) n[k] = (o >> k) & 1 ? g.nv1[k] - g.vsplit[k] : g.vsplit[k];
-  const int loc = j - first, r = loc / n[0], l2 = r / n[1];
+  const int loc = j - (SELECT ? first : g.voct[o]), r = loc / n[0], l2 = r / n[1];
   const int l[3] = {loc - r * n[0], r - l2 * n[1], l2};
 #pragma unroll
   for (int k = 0; k < 3; ++k) b[k] = l[k] + ((o >> k) & 1 ? g.vsplit[k] : 0);
 }
 
+template <bool SELECT = true>
 __device__ __forceinline__ Vel velocity_of(const DevGeom& g, int j) {
   Vel v;
-  slot_nodes(g, j, v.b);
+  slot_nodes<SELECT>(g, j, v.b);
   double w = 1.0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {

@@ -137,7 +137,7 @@ __device__ __forceinline__ void hex_walk(table_ptr<StageArgs> ap, const int chun
   const int j = chunk * H::VB + wave * 16 + v;
   const bool valid = j < nv;
   const int jj = valid ? j : nv - 1;
-  Vel vel = velocity_of(g, jj);
+  Vel vel = velocity_of<false>(g, jj);
   if (!valid) vel.w = 0.0;
 
   const RowPick rp = row_pick(A0, chunk, NS);
@@ -166,7 +166,7 @@ __device__ __forceinline__ void hex_walk(table_ptr<StageArgs> ap, const int chun
   bool up[2], pos[3];
   {
     int b0[3];
-    slot_nodes(g, chunk * H::VB < nv ? chunk * H::VB : nv - 1, b0);
+    slot_nodes<false>(g, chunk * H::VB < nv ? chunk * H::VB : nv - 1, b0);
 #pragma unroll
     for (int k = 0; k < 2; ++k) up[k] = (g.vlo[k] + b0[k] * g.du[k]) * g.scale[k] > 0.0;
   }
@@ -197,7 +197,7 @@ __device__ __forceinline__ void hex_walk(table_ptr<StageArgs> ap, const int chun
     right = pos[k] != wall;
     if (wall) {  // the own element at the mirrored velocity
       int bm[3];
-      slot_nodes(g, jj, bm);
+      slot_nodes<false>(g, jj, bm);
       bm[k] = g.nv1[k] - 1 - bm[k];
       return e * estride + lane_off(vel_slot(g, bm));
     }
