@@ -207,6 +207,9 @@ __device__ __forceinline__ void xwalk(table_ptr<StageArgs> ap, const int chunk, 
   }
   load_element(e_row + ex);
 
+  // limiter counters of the wave over the run (shared only behind it: without
+  // collisions an element has no barrier between two waves' limiters)
+  int hits = 0, bad = 0;
   for (int s = 0; s < n; ++s, ex += dx) {
     asm volatile("" : "+s"(ap));
     const int64_t e = e_row + ex, eoff = e * estride + own_off;
@@ -360,7 +363,6 @@ __device__ __forceinline__ void xwalk(table_ptr<StageArgs> ap, const int chunk, 
       else o[q] = ca * fnv[q] + acc[q];
     }
     const DevOpsT<CT>& OP = ops_of<CT>(A);
-    __shared__ LimiterCounts lim;
     if (A.limiter) {
       CT fmin = o[0];
 #pragma unroll
@@ -373,7 +375,8 @@ __device__ __forceinline__ void xwalk(table_ptr<StageArgs> ap, const int chunk, 
 #pragma unroll
         for (int q = 0; q < NS; ++q) o[q] = mean + beta * (o[q] - mean);
       }
-      limiter_count(lim, __popcll(__ballot(hit)), __popcll(__ballot(hit && !(mean > (CT)0))), tid);
+      hits += __popcll(__ballot(hit));
+      bad += __popcll(__ballot(hit && !(mean > (CT)0)));
     }
     if (INC && !A.out_full) {
       if constexpr (INC) {
@@ -422,7 +425,12 @@ __device__ __forceinline__ void xwalk(table_ptr<StageArgs> ap, const int chunk, 
       for (int w = 1; w < kBlock / 64; ++w) sum += red[w * part_rows<NS>() * 5 + t];
       A.partials[((int64_t)chunk * A.g.nx + e * NS) * 5 + t] = sum;
     }
-    if (A.limiter) limiter_add(lim, A.diag, tid);
+  }
+  __shared__ LimiterCounts lim;
+  if (args().limiter) {
+    limiter_count(lim, hits, bad, tid);
+    lds_barrier();
+    limiter_add(lim, args().diag, tid);
   }
   if (tid == 0 && count) atomicAdd(&args().diag[4], 1ull);
 }
