@@ -676,6 +676,8 @@ static hipError_t hex_dispatch(int mode, bool inc, const StageArgs& A, size_t ta
         hipLaunchKernelGGL((k_stage<3, P, ST, 1>), grid, block, lds, s, A);
       } else if (mode == 2) {
         hipLaunchKernelGGL((k_moments<3, P, ST>), grid, block, lds, s, A);
+      } else if constexpr (P == 3) {  // canonical source: not built (64 nodes spill)
+        return hipErrorInvalidValue;
       } else if (mode == 3) {
         hipLaunchKernelGGL((k_residual<3, P, ST>), grid, block, lds, s, A);
       } else {

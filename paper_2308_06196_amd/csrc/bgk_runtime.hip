@@ -578,6 +578,17 @@ void brick_order(const int32_t* ne, std::vector<int32_t>& out) {
               out.push_back(x + ne[0] * (y + ne[1] * z));
 }
 
+// Whether the residual of a canonical device array is formed in place: not for
+// p = 3 hexahedra in FP32, whose 64 nodes of one lane then have addresses of
+// their own (nodes are nv values apart, a run-time stride): 356 spilled
+// registers, and the call took 8.07 ms on 10 x 8 x 8 elements with 16^3
+// velocities where the copy to the internal layout, whose node offsets are
+// immediates, takes 1.40 (16^3 elements 51.3 / 9.04 ms, 3^3 on 8^3 186 / 48 us). The
+// other kernels gain from it (FP32 p = 2 hexahedra 581 / 457 us on 10 x 8 x 8).
+bool reads_canonical(const bgk_solver* s) {
+  return !(s->pb.dim == 3 && s->pb.order == 3 && s->precision == BGK_FP32);
+}
+
 // Residual L(f_in) of a canonical device array that r_out does not overlap:
 // moments, equilibria, wall densities and residual read f_in in place, in its
 // own velocity order, so nothing is converted first and the residual's rows
@@ -940,7 +951,7 @@ bgk_status bgk_residual(bgk_solver* s, const double* f_in, double* r_out, int32_
   }
   const int64_t n = s->L.nx * s->L.nv;
   const void* fin = s->state();
-  if (f_in && where == BGK_DEVICE && !overlap(f_in, r_out, n)) {
+  if (f_in && where == BGK_DEVICE && reads_canonical(s) && !overlap(f_in, r_out, n)) {
     s->partials_valid = false;  // the partials now belong to f_in
     return residual_canonical(s, f_in, r_out);
   }
@@ -1308,7 +1319,7 @@ bgk_status bgk_residual_noalloc(const bgk_problem* pb, const double* f_in, doubl
                      row_cols_all(s.g));
   HIP_TRY(hipGetLastError());
   const int64_t n = L.nx * L.nv;
-  if (!overlap(f_in, r_out, n)) return residual_canonical(&s, f_in, r_out);
+  if (reads_canonical(&s) && !overlap(f_in, r_out, n)) return residual_canonical(&s, f_in, r_out);
   HIP_TRY(launch_to_storage(s.precision, s.g, f_in, s.f(0), 0, n, s.stream));
   if ((st = moments_of(&s, s.f(0)))) return st;
   NewtonArgs N = newton_args(&s);
