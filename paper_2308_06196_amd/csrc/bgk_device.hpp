@@ -459,6 +459,31 @@ struct Source<true, ST> {
   }
 };
 
+// Residual output, read by nothing here again: past the caches where a wave's
+// store covers whole 64-byte sectors, so that the neighbours' nodes stay in them
+// (residual of the installed state, us, plain / past the caches: 10 x 8 x 8 p = 1
+// elements on 16^3 velocities 129 / 85, 20 x 24 p = 3 in FP32 127 / 83, 16^3 p = 3
+// hexahedra in FP32 4459 / 3738). Partial sectors need the L2 to be joined
+// (301 p = 3 line elements on 15 x 17 x 19 37 / 50, 2^3 p = 3 hexahedra in FP32 on
+// 24^3, octants of 12, 37 / 61). ALWAYS: of a canonical source, in whole rows.
+template <bool ALWAYS = false>
+__device__ __forceinline__ void residual_store(bool whole, double* p, double v) {
+  if constexpr (ALWAYS) {
+    __builtin_nontemporal_store(v, p);
+  } else if (whole) {
+    asm volatile("");  // (else the branches' stores are joined, without the hint)
+    __builtin_nontemporal_store(v, p);
+    asm volatile("");
+  } else {
+    *p = v;
+  }
+}
+// Whether consecutive slots fill whole sectors of the canonical layout: an octant
+// holds runs of vsplit[0] or nv1[0] - vsplit[0] velocities along x.
+__device__ __forceinline__ bool whole_sectors(const DevGeom& g) {
+  return ((g.vsplit[0] | g.nv1[0]) & 7) == 0;
+}
+
 template <typename ST> struct Compute;
 template <> struct Compute<double> { using T = double; };
 template <> struct Compute<float> { using T = float; };
@@ -1286,6 +1311,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
   const int cx = vel.b[0] - rp.x0, oy = rp.nx + vel.b[1] - rp.y0,
             oz = rp.nxy + vel.b[2] - rp.z0;
   double* oe1 = nullptr;  // residual output (canonical layout, MODE 1)
+  const bool whole = MODE == 1 && whole_sectors(g);
   if constexpr (MODE == 1) {
     const int jc = vel.b[0] + g.nv1[0] * (vel.b[1] + g.nv1[1] * vel.b[2]);
     oe1 = (double*)A.out + (e - A.out_e0) * NS * nv + jc;
@@ -1302,7 +1328,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
     for (int i = 0; i < NS; ++i) {
       const double c = collision_term(tab + i * rp.ncols, cx, oy, oz, rp.ncols, (double)f[i]);
       if constexpr (MODE == 1) {
-        if (valid) __builtin_nontemporal_store(c - (double)acc[i], &oe1[(int64_t)i * nv]);
+        if (valid) residual_store<CAN>(whole, &oe1[(int64_t)i * nv], c - (double)acc[i]);
       } else if constexpr (!kFold) {
         const CT r = fmaf(-dt, acc[i], f[i]);
         const CT b32 = MODE == 0 ? fmaf(ca, fnv[i], cb * r) : cb * r;
@@ -1317,7 +1343,7 @@ __device__ __forceinline__ void stage_item(const StageArgs& A, const int chunk, 
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
       if constexpr (MODE == 1) {
-        if (valid) __builtin_nontemporal_store(-(double)acc[i], &oe1[(int64_t)i * nv]);
+        if (valid) residual_store<CAN>(whole, &oe1[(int64_t)i * nv], -(double)acc[i]);
       } else if constexpr (!kFold) {
         const CT r = fmaf(-dt, acc[i], f[i]);
         o[i] = MODE == 0 ? fmaf(ca, fnv[i], cb * r) : cb * r;

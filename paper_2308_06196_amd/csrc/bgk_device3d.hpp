@@ -312,18 +312,19 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
   const double* tp = tab + pl * P2 * rp.ncols;  // rows of this lane's plane
   const int jc = vel.b[0] + g.nv1[0] * (vel.b[1] + g.nv1[1] * vel.b[2]);
   double* oe1 = (double*)A.out + ((e - A.out_e0) * NS + pl * P2) * nv + jc;
+  const bool whole = whole_sectors(g);  // (a wave stores 16 velocities of a node)
   if (A.collide) {  // uniform: rows beyond the first batch, then the relaxation
     table_rest<kU>(tab, et, rp, tid);
     lds_barrier();
 #pragma unroll
     for (int q = 0; q < P2; ++q) {
       const double c = collision_term(tp + q * rp.ncols, cx, oy, oz, rp.ncols, (double)f[q]);
-      if (act) oe1[(int64_t)q * nv] = c - (double)acc[q];
+      if (act) residual_store(whole, &oe1[(int64_t)q * nv], c - (double)acc[q]);
     }
   } else {
 #pragma unroll
     for (int q = 0; q < P2; ++q)
-      if (act) oe1[(int64_t)q * nv] = -(double)acc[q];
+      if (act) residual_store(whole, &oe1[(int64_t)q * nv], -(double)acc[q]);
   }
   if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
 }
