@@ -55,8 +55,10 @@ __device__ __forceinline__ double team_sum(double x) {
 // chunks of the moment partials and the nodes of each one-dimensional sum;
 // the 5x5 solve is repeated identically in every lane of the team. Large
 // meshes use 2- or 4-lane teams (less redundant solve work), small ones
-// 16-lane teams (enough waves to fill the device).
-template <int kTeam>
+// 16-lane teams (enough waves to fill the device). The one-dimensional sums run
+// over the three axes together, up to the longest one; with SPLIT up to the
+// shortest one, and each axis' rest alone (newton_split says where).
+template <int kTeam, bool SPLIT>
 __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t node_raw) {
   const DevGeom& g = A.g;
   const int r = threadIdx.x % kTeam;
@@ -69,7 +71,9 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
   double Q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   const double* pp = A.partials + node * 5;  // chunk c at pp[c * nx * 5]
   constexpr int kH = kTeam >= 16 ? 1 : 2;
-  const int nmax = max(g.nv1[0], max(g.nv1[1], g.nv1[2]));
+  constexpr int kStep = kH * kTeam;
+  const int njoint = SPLIT ? (min(g.nv1[0], min(g.nv1[1], g.nv1[2])) + kStep - 1) / kStep * kStep
+                           : max(g.nv1[0], max(g.nv1[1], g.nv1[2]));
   // chunk partials: batches of kPB chunks per lane, all loads of a batch in
   // flight (chunks past the last read that one again, with weight 0: a
   // conditional load becomes a branch of its own)
@@ -129,7 +133,7 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
       for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int n = 0; n < 5; ++n) S[c][n] = 0.0;
-      for (int b0 = r; b0 < nmax; b0 += kH * kTeam) {
+      for (int b0 = r; b0 < njoint; b0 += kH * kTeam) {
 #pragma unroll
         for (int h = 0; h < kH; ++h) {
 #pragma unroll
@@ -137,6 +141,21 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
             const int b = b0 + h * kTeam, N = g.nv1[c], bb = b < N ? b : N - 1;
             const double u = g.vlo[c] + bb * g.du[c], u2 = u * u;
             const double wc = b >= N ? 0.0 : g.du[c] * (bb == 0 || bb == N - 1 ? 0.5 : 1.0);
+            const double t = wc * exp(al[1 + c] * u + al[4] * (0.5 * u2));
+            S[c][0] += t;
+            S[c][1] += t * u;
+            S[c][2] += t * u2;
+            S[c][3] += t * u2 * u;
+            S[c][4] += t * u2 * u2;
+          }
+        }
+      }
+      if constexpr (SPLIT) {  // what is left of the longer axes
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          for (int b = njoint + r; b < g.nv1[c]; b += kTeam) {
+            const double u = g.vlo[c] + b * g.du[c], u2 = u * u;
+            const double wc = g.du[c] * (b == g.nv1[c] - 1 ? 0.5 : 1.0);
             const double t = wc * exp(al[1 + c] * u + al[4] * (0.5 * u2));
             S[c][0] += t;
             S[c][1] += t * u;
@@ -240,7 +259,7 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
   // form the collision term as Ex[bx] Ey[by] Ez[bz] - f / tau
   double* row = (double*)A.etab + node * g.tabw;
   const int off1 = g.nv1[0], off2 = off1 + g.nv1[1], off = off2 + g.nv1[2];
-  for (int b0 = r; b0 < nmax; b0 += kH * kTeam) {
+  for (int b0 = r; b0 < njoint; b0 += kH * kTeam) {
 #pragma unroll
     for (int h = 0; h < kH; ++h) {
 #pragma unroll
@@ -249,6 +268,16 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
         const double u = g.vlo[c] + b * g.du[c];
         const double v = exp((c == 0 ? al[0] : 0.0) + al[1 + c] * u + al[4] * (0.5 * u * u));
         if (active && b < g.nv1[c]) row[(c == 0 ? 0 : c == 1 ? off1 : off2) + b] = c == 0 ? v * itau : v;
+      }
+    }
+  }
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      for (int b = njoint + r; b < g.nv1[c]; b += kTeam) {
+        const double u = g.vlo[c] + b * g.du[c];
+        const double v = exp((c == 0 ? al[0] : 0.0) + al[1 + c] * u + al[4] * (0.5 * u * u));
+        if (active) row[(c == 0 ? 0 : c == 1 ? off1 : off2) + b] = c == 0 ? v * itau : v;
       }
     }
   }
@@ -274,20 +303,21 @@ __device__ __forceinline__ void newton_item(const NewtonArgs& A, const int64_t n
   }
 }
 
-template <int kTeam>
-__global__ void __launch_bounds__(256) k_newton(const NewtonArgs A) {
-  newton_item<kTeam>(A, ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kTeam);
+template <int kTeam, bool SPLIT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+    k_newton(const NewtonArgs A) {
+  newton_item<kTeam, SPLIT>(A, ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kTeam);
 }
 
 // Equilibrium solves of the batch members of one team size: whole work-groups
 // of 256 lanes per member, so that a work-group's arguments are uniform; the
 // grid is the list's work-group count.
-template <int kTeam>
+template <int kTeam, bool SPLIT>
 __global__ void __launch_bounds__(256) k_newton_batch(table_ptr<NewtonArgs> args,
                                                       table_ptr<BatchList> list) {
   const int32_t t = blockIdx.x;
   const int m = batch_member(list->newton_off, list->n, t);
-  newton_item<kTeam>(table_entry(args, list->slot[m]),
+  newton_item<kTeam, SPLIT>(table_entry(args, list->slot[m]),
                      ((int64_t)(t - list->newton_off[m]) * 256 + threadIdx.x) / kTeam);
 }
 
@@ -901,12 +931,20 @@ hipError_t launch_newton(const NewtonArgs& A, hipStream_t s) {
   // (262,144 nodes on 16^3: 108 us against 124 with 4 and 280 with 16; 216,000
   // nodes on 20^3: 145 against 154)
   const int team = newton_team(A.g.nx);
-  if (team == 2)
-    hipLaunchKernelGGL(k_newton<2>, dim3(grid_of(A.g.nx * 2, 256)), dim3(256), 0, s, A);
-  else if (team == 4)
-    hipLaunchKernelGGL(k_newton<4>, dim3(grid_of(A.g.nx * 4, 256)), dim3(256), 0, s, A);
-  else
-    hipLaunchKernelGGL(k_newton<16>, dim3(grid_of(A.g.nx * 16, 256)), dim3(256), 0, s, A);
+  const dim3 grid(grid_of(A.g.nx * team, 256)), block(256);
+#define BGK_NEWTON(T)                                                   \
+  if (newton_split(A.g))                                                \
+    hipLaunchKernelGGL((k_newton<T, true>), grid, block, 0, s, A);      \
+  else                                                                  \
+    hipLaunchKernelGGL((k_newton<T, false>), grid, block, 0, s, A)
+  if (team == 2) {
+    BGK_NEWTON(2);
+  } else if (team == 4) {
+    BGK_NEWTON(4);
+  } else {
+    BGK_NEWTON(16);
+  }
+#undef BGK_NEWTON
   return hipGetLastError();
 }
 
@@ -959,18 +997,24 @@ hipError_t launch_stage_batch(int precision, int dim, int order, int stage, cons
   return hipGetLastError();
 }
 
-hipError_t launch_newton_batch(int team, const NewtonArgs* args, const BatchList* list,
-                               unsigned grid, hipStream_t s) {
+hipError_t launch_newton_batch(int team, bool split, const NewtonArgs* args,
+                               const BatchList* list, unsigned grid, hipStream_t s) {
   if (grid == 0) return hipSuccess;
-  if (team == 16)
-    hipLaunchKernelGGL(k_newton_batch<16>, dim3(grid), dim3(256), 0, s, (table_ptr<NewtonArgs>)args,
-                       (table_ptr<BatchList>)list);
-  else if (team == 4)
-    hipLaunchKernelGGL(k_newton_batch<4>, dim3(grid), dim3(256), 0, s, (table_ptr<NewtonArgs>)args,
-                       (table_ptr<BatchList>)list);
-  else
-    hipLaunchKernelGGL(k_newton_batch<2>, dim3(grid), dim3(256), 0, s, (table_ptr<NewtonArgs>)args,
-                       (table_ptr<BatchList>)list);
+#define BGK_NEWTON(T)                                                                    \
+  if (split)                                                                             \
+    hipLaunchKernelGGL((k_newton_batch<T, true>), dim3(grid), dim3(256), 0, s,           \
+                       (table_ptr<NewtonArgs>)args, (table_ptr<BatchList>)list);         \
+  else                                                                                   \
+    hipLaunchKernelGGL((k_newton_batch<T, false>), dim3(grid), dim3(256), 0, s,          \
+                       (table_ptr<NewtonArgs>)args, (table_ptr<BatchList>)list)
+  if (team == 16) {
+    BGK_NEWTON(16);
+  } else if (team == 4) {
+    BGK_NEWTON(4);
+  } else {
+    BGK_NEWTON(2);
+  }
+#undef BGK_NEWTON
   return hipGetLastError();
 }
 
@@ -1006,6 +1050,23 @@ hipError_t launch_wall_rho_batch(int stage, const WallArgs* args, const BatchLis
 }
 
 int newton_team(int64_t nx) { return nx >= 131072 ? 2 : nx >= 8192 ? 4 : 16; }
+
+// The three axes' sums together cost a launch the longest axis three times, but
+// their exponentials overlap; so only where the axes together are well below that
+// (us a launch, one axis after another / jointly / split: 64 x 8 x 8 velocities on
+// 175,616 nodes 189 / 293 / 169, on 16,384 42 / 39 / 29, on 96 19.0 / 18.9 / 16.5; 32 x
+// 16 x 8 on 175,616 130 / 142 / 110, on 96, where the joint one stays, 17.7 / 15.2 /
+// 16.2; a grid of 16^3 takes 0.6 us more split).
+bool newton_split(const DevGeom& g) {
+  const int team = newton_team(g.nx), step = team == 16 ? 16 : 2 * team;
+  int sum = 0, longest = 0;
+  for (int c = 0; c < 3; ++c) {
+    const int n = (g.nv1[c] + step - 1) / step * step;
+    sum += n;
+    longest = std::max(longest, n);
+  }
+  return sum < (team == 16 ? 0.6 : 0.8) * 3 * longest;
+}
 
 hipError_t launch_reduce_partials(const DevGeom& g, const double* partials, double* Q,
                                   hipStream_t s) {

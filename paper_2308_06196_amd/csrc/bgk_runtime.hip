@@ -1355,10 +1355,10 @@ constexpr int kMaxFamilies = 24;   // dimension 1-2 x order 1-3 x FP64/FP32 x ro
 // its solo launches: the 2-D boxes of the serving mix above about 4e8 DOF
 // (the FP64 column sweep is some 8 % faster than the per-element items there).
 constexpr int64_t kSoloUnits = 8192;
-constexpr int kTeamLists = 3;      // equilibrium teams of 16, 4, 2 lanes
+constexpr int kTeamLists = 6;      // equilibrium teams of 16, 4, 2 lanes, then those of split sums
 constexpr int kAllList = kMaxFamilies + kTeamLists;  // every member (wall densities)
 constexpr int kListsPerSub = kAllList + 1;
-constexpr int kTeamOfList[kTeamLists] = {16, 4, 2};
+constexpr int kTeamOfList[kTeamLists] = {16, 4, 2, 16, 4, 2};
 
 struct TableLayout {
   size_t args, nargs, wargs, lists, total;
@@ -1379,7 +1379,10 @@ TableLayout table_layout() {
   return t;
 }
 
-int team_index(int team) { return team == 16 ? 0 : team == 4 ? 1 : 2; }
+int team_index(const DevGeom& g) {
+  const int team = newton_team(g.nx);
+  return (team == 16 ? 0 : team == 4 ? 1 : 2) + (newton_split(g) ? 3 : 0);
+}
 
 // work units of a member: stage work items, equilibrium work-groups
 int64_t member_units(const bgk_solver* s) {
@@ -1513,7 +1516,7 @@ bgk_status upload_tables(bgk_batch* b) {
       const bgk_solver* s = m.s;
       const int64_t wf = s->wall.nside ? s->wall.blk0[s->wall.nside] : 0;
       const int64_t wr = s->wall.nside ? (s->wall.npoints + 255) / 256 : 0;
-      const int ls[3] = {m.family, kMaxFamilies + team_index(newton_team(s->L.nx)), kAllList};
+      const int ls[3] = {m.family, kMaxFamilies + team_index(s->g), kAllList};
       for (int l : ls) {
         BatchList& B = L[l];
         const int i = B.n++;
@@ -1547,7 +1550,8 @@ bgk_status replay(bgk_batch* b) {
     if (b->units[sub][kAllList][1] == 0) break;  // no member takes this sub-step
     for (int stage = 0; stage < 3 && e == hipSuccess; ++stage) {
       for (int t = 0; t < kTeamLists && e == hipSuccess; ++t)
-        e = launch_newton_batch(kTeamOfList[t], b->d_nargs(), b->d_list(sub, kMaxFamilies + t),
+        e = launch_newton_batch(kTeamOfList[t], t >= 3, b->d_nargs(),
+                                b->d_list(sub, kMaxFamilies + t),
                                 (unsigned)b->units[sub][kMaxFamilies + t][1], b->stream);
       for (size_t f = 0; f < b->fams.size() && e == hipSuccess; ++f)
         e = launch_wall_flux_batch(b->fams[f].precision, b->fams[f].dim, b->fams[f].order, stage,
