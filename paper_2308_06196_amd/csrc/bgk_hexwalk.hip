@@ -45,6 +45,10 @@ static int resident_walks(int precision, int ncols, int tx) {
              : resident_groups(k_stage_walk<float, 0, true>, HexWalk::lds_bytes<float>(ncols, tx));
 }
 
+// LDS that one walking work-group may take: a compute unit's 160 KB less its
+// line operators.
+constexpr int kWalkLds = 160 * 1024 - 4 * (int)sizeof(LineOps);
+
 // Velocity chunks that hold velocities of more than one octant.
 static int mixed_chunks(const DevGeom& g) {
   const int vb = HexWalk::VB;
@@ -123,8 +127,15 @@ void walk_tile(const DevGeom& g, int precision, int ncols, int* tx_out, int* ty_
   if (const char* env = getenv("BGK_WALK_TILE")) {
     int x = 0, y = 0;
     if (sscanf(env, "%dx%d", &x, &y) == 2 && x > 0 && y > 0) {
-      tx = std::min(std::min(x, nx), 16);
+      tx = std::min(x, nx);
       ty = std::min(y, ny);
+      // (a row's y traces must fit a compute unit's LDS beside the equilibrium rows,
+      // those of up to five elements always do)
+      auto lds = [&] {
+        return precision == 0 ? HexWalk::lds_bytes<double>(ncols, tx)
+                              : HexWalk::lds_bytes<float>(ncols, tx);
+      };
+      while (tx > 1 && lds() > kWalkLds) --tx;
     }
   }
   *tx_out = tx;
