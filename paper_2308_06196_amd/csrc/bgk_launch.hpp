@@ -30,7 +30,7 @@ void walk_tile(const DevGeom& g, int precision, int ncols, int* tx, int* ty);
 // mesh row per work-group (k_stage_rows). rows_pay: whether a solver of this
 // mesh uses it; rows_runs: work items per velocity chunk; rows_tab_bytes: LDS
 // of the equilibrium rows.
-bool rows_pay(const DevGeom& g, bool collide);
+bool rows_pay(const DevGeom& g, int precision, bool collide);
 int64_t rows_runs(const DevGeom& g);
 size_t rows_tab_bytes(const DevGeom& g, bool collide);
 hipError_t launch_rows(int precision, const StageArgs& A, hipStream_t s);

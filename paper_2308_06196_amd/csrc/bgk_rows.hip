@@ -1,46 +1,19 @@
 // bgk_rows.hip -- instantiations and launchers of the stage kernels that run
 // several elements of a mesh row per work-group.
-#include <cstdlib>
-
 #include "bgk_launch.hpp"
-#include "bgk_rows.hpp"
+#include "bgk_rows_rule.hpp"
 
 namespace bgk {
-
-#define BGK_ROWS_CASES \
-  BGK_CASE(1, 1) BGK_CASE(1, 2) BGK_CASE(1, 3) BGK_CASE(2, 1) BGK_CASE(2, 2)
-
-static int row_elems_of(const DevGeom& g) {
-  switch (g.dim * 10 + (g.n1 - 1)) {
-#define BGK_CASE(D, P) \
-  case D * 10 + P:     \
-    return row_elems<D, P>();
-    BGK_ROWS_CASES
-#undef BGK_CASE
-    default:
-      return 0;
-  }
-}
 
 int64_t rows_runs(const DevGeom& g) {
   const int E = row_elems_of(g);
   return (int64_t)((g.nelem[0] + E - 1) / E) * (g.dim == 2 ? g.nelem[1] : 1);
 }
 
-size_t rows_tab_bytes(const DevGeom& g, bool collide) {
-  return collide ? (size_t)row_elems_of(g) * g.ns * g.tabw * sizeof(double) : 0;
-}
+size_t rows_tab_bytes(const DevGeom& g, bool collide) { return row_tab_bytes(g, collide); }
 
-// Runs need enough work items to fill the device: from 1024 per-element ones
-// (element x velocity chunk) on they measured faster (FP64, us per launch, per
-// element / runs: 512-element tube on 8^3 velocities, 1024 items, 13.8 / 12.2;
-// 128-element tube on 16^3, 2048 items, 19.6 / 14.6; 32-element tube on 16^3,
-// 512 items, 10.2 / 11.7; 16^2 box on 8^3, 512 items, 13.8 / 14.6).
-bool rows_pay(const DevGeom& g, bool collide) {
-  if (row_elems_of(g) == 0 || rows_tab_bytes(g, collide) > (size_t)kMaxTabBytes) return false;
-  // BGK_ROWS overrides the choice (0 or 1)
-  if (const char* env = getenv("BGK_ROWS")) return atoi(env) != 0;
-  return g.ne * g.nchunk >= 1024;
+bool rows_pay(const DevGeom& g, int precision, bool collide) {
+  return row_runs_pay(g, precision, collide);
 }
 
 template <int D, int P, typename ST>

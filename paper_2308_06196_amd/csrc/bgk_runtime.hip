@@ -756,7 +756,7 @@ void init_solver(bgk_solver* s, const bgk_problem* pb, char* ws, hipStream_t str
     else if (s->L.wall_points == 0)
       s->walk_tx = xwalk_length(g, pb->precision);
   }
-  if (brick) s->rows = rows_pay(g, pb->mu_ref > 0.0);
+  if (brick) s->rows = rows_pay(g, pb->precision, pb->mu_ref > 0.0);
   if (brick && !s->walk_tx) s->sweep_seg = sweep_segment(g, pb->precision, pb->mu_ref > 0.0);
   if (brick) {
     // XCDs sharing a velocity chunk in the stage launches (xcd_chunk_remap):
