@@ -51,5 +51,20 @@ def build(verbose: bool = True) -> str:
     return LIB
 
 
+def build_checks(only_missing: bool = False) -> str:
+    """Library of device functions that a test calls directly (tests/*.hip)."""
+    src = os.path.join(ROOT, "tests", "bf16_pair_check.hip")
+    lib = os.path.join(ROOT, "tests", "libbf16pair.so")
+    if not (only_missing and os.path.exists(lib)):
+        tmp = lib + ".tmp"
+        r = subprocess.run([HIPCC, *FLAGS, "-shared", src, "-o", tmp], capture_output=True, text=True)
+        if r.returncode != 0:
+            sys.stderr.write(r.stdout + r.stderr)
+            raise RuntimeError(f"hipcc failed for {src}")
+        os.replace(tmp, lib)
+    return lib
+
+
 if __name__ == "__main__":
     build()
+    build_checks()
