@@ -4,70 +4,66 @@
 //
 // Used at p = 3 with FP64 storage and BF16 increments (the RK stages of these
 // solvers are k_stage_walk's, bgk_hexwalk.hpp); the other hexahedra run the
-// one-lane-per-velocity kernels of bgk_device.hpp. Here a group of G lanes
-// (G = 2 for p = 1, 4 for p = 2, 3) shares one velocity and lane g of the
-// group owns the z-plane a_z = g of the element: (p+1)^2 nodes. The x and
-// y operators are lane-local exactly as for quadrilaterals; the z-derivative
-// and the z-face traces need the other planes of the same column, which come
-// from the other lanes of the group by DPP quad permutations (no LDS, no
-// barriers). A work-group of 256 lanes covers 256 / G consecutive velocity slots
-// of one element. Lanes with g >= p+1 (p = 2) load nothing and store nothing.
+// one-lane-per-velocity kernels of bgk_device.hpp. Here the four lanes of a quad
+// share one velocity and lane a_z of the quad owns that z-plane of the element:
+// 16 nodes. The x and y operators are lane-local exactly as for quadrilaterals; the
+// z-derivative and the z-face traces need the other planes of the same column,
+// which come from the other lanes of the quad by DPP permutations (no LDS, no
+// barriers). A work-group of 256 lanes covers 64 consecutive velocity slots of one
+// element.
 #pragma once
 
 #include "bgk_device.hpp"
 
 namespace bgk {
 
-template <int P> struct Plane3 {
-  static constexpr int N1 = P + 1;
-  static constexpr int G = N1 <= 2 ? 2 : 4;   // lanes per velocity
+struct Plane3 {
+  static constexpr int N1 = 4;
+  static constexpr int G = N1;                 // lanes per velocity
   static constexpr int VB = kBlock / G;        // velocities per work-group
   static constexpr int P2 = N1 * N1;           // nodes per plane
   static constexpr int NS = N1 * N1 * N1;
 };
 
-// Sum over the G lanes of a group (partners lane ^ 1, lane ^ 2; every lane ends
-// with the same bits).
-template <int G, typename T>
-__device__ __forceinline__ T group_allsum(T x) {
+// Sum over the lanes of a quad (partners lane ^ 1, lane ^ 2; every lane ends with
+// the same bits).
+template <typename T>
+__device__ __forceinline__ T quad_allsum(T x) {
   x += quad_xor<1>(x);
-  if constexpr (G == 4) x += quad_xor<2>(x);
+  x += quad_xor<2>(x);
   return x;
 }
 
 // Moment partials of one element on the matrix cores (FP64 MFMA), as in the
 // 1-D/2-D kernels: per wave and per plane pl, P[q][m] = sum over the wave's
-// 64 / G velocities v of f[pl][q][v] (w psi_m)(v), a (p+1)^2 x K by K x 5
-// contraction on the matrix cores (wave_moments_4x4, one 16-row tile per
+// 16 velocities v of f[pl][q][v] (w psi_m)(v), a 16 x 16 by 16 x 5 contraction on the matrix cores (wave_moments_4x4, one 16-row tile per
 // plane). Every lane stages its plane's values, the first lane of each
 // velocity group stages w psi of that velocity; the four waves' results are
-// added in a fixed order. `stage` is mfma3_lds_bytes<P, ST>() bytes, `red`
+// added in a fixed order. `stage` is mfma3_lds_bytes<ST>() bytes, `red`
 // 4 x NS x 5 doubles.
-template <int P, typename ST>
+template <typename ST>
 constexpr int mfma3_lds_bytes() {
-  constexpr int G = Plane3<P>::G, K = 64 / G, RS = K + 2;
+  constexpr int G = Plane3::G, K = 64 / G, RS = K + 2;
   return (kBlock / 64) * (K * 5 * (int)sizeof(double) + G * 16 * RS * (int)sizeof(ST));
 }
 
-template <int P, typename ST, typename CT>
-__device__ __forceinline__ void plane_partials_mfma(const CT (&fv)[Plane3<P>::P2], const Vel& vel,
+template <typename ST, typename CT>
+__device__ __forceinline__ void plane_partials_mfma(const CT (&fv)[Plane3::P2], const Vel& vel,
                                                     double* __restrict__ partials, int64_t node0,
                                                     int64_t nx, int chunk, int lp,
                                                     unsigned char* stage, double* red,
                                                     const int tid) {
-  using PL = Plane3<P>;
+  using PL = Plane3;
   constexpr int N1 = PL::N1, G = PL::G, P2 = PL::P2, NS = PL::NS;
   constexpr int K = 64 / G, RS = K + 2;
-  static_assert(P2 <= 16, "the nodes of a plane fill at most one 16-row tile");
+  static_assert(P2 == 16, "the nodes of a plane fill one 16-row tile");
   const int lane = tid & 63, wave = tid >> 6;
   const int vw = lane / G;  // velocity of this lane inside the wave
   double* ps = reinterpret_cast<double*>(stage) + wave * K * 5;
   ST* gw = reinterpret_cast<ST*>(stage + (kBlock / 64) * K * 5 * sizeof(double)) +
            wave * G * 16 * RS;
-  if (lp < N1) {
 #pragma unroll
-    for (int q = 0; q < P2; ++q) gw[(lp * 16 + q) * RS + vw] = (ST)fv[q];
-  }
+  for (int q = 0; q < P2; ++q) gw[(lp * 16 + q) * RS + vw] = (ST)fv[q];
   if (lp == 0) {
     const double psi4 = 0.5 * (vel.u[0] * vel.u[0] + vel.u[1] * vel.u[1] + vel.u[2] * vel.u[2]);
     ps[vw * 5 + 0] = vel.w;
@@ -94,13 +90,13 @@ __device__ __forceinline__ void plane_partials_mfma(const CT (&fv)[Plane3<P>::P2
 // One work item (element e x velocity chunk) of the residual L(f) in FP64, of
 // the internal state or a canonical array (see Source; the
 // RK stages of these elements are k_stage_walk's, bgk_hexwalk.hpp).
-template <int P, typename ST, bool CAN>
+template <typename ST, bool CAN>
 __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chunk, const int64_t e,
                                                const bool count) {
   using CT = typename Compute<ST>::T;
   using Src = Source<CAN, ST>;
   using FT = typename Src::T;
-  using PL = Plane3<P>;
+  using PL = Plane3;
   constexpr bool kMfma = sizeof(CT) == 4;
   constexpr int N1 = PL::N1, G = PL::G, VB = PL::VB, P2 = PL::P2, NS = PL::NS;
   __shared__ FaceRows<CT> frows[kBlock / 64];
@@ -119,11 +115,9 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
   const int S = g.tabw;
   const int64_t node0 = e * NS;
 
-  const int lp = tid % G;                        // plane owned by this lane
-  const bool live = lp < N1;
-  const int pl = live ? lp : N1 - 1;             // address plane (idle lanes)
+  const int lp = tid % G;  // plane owned by this lane
   const int j = chunk * VB + tid / G;
-  const bool act = j < nv && live;
+  const bool act = j < nv;
   const int jj = j < nv ? j : (int)nv - 1;
   const Vel vel = velocity_of(g, jj);
 
@@ -165,7 +159,7 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
       src_e = e + (int64_t)(nk - ek[k]) * stride;
     }
     use_right[k] = (pos[k] != wall);
-    src[k] = fin + Src::offset(g, src_e, pl * P2, src_j);
+    src[k] = fin + Src::offset(g, src_e, lp * P2, src_j);
   }
 
   // first batch of row loads: 4 x 256 entries for FP32 arithmetic, whose
@@ -182,7 +176,7 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
       tv[u] = et[rp.offset(t < rp.count ? t : rp.count - 1)];
     }
   }
-  const FT* fe = fin + Src::offset(g, e, pl * P2, jj);
+  const FT* fe = fin + Src::offset(g, e, lp * P2, jj);
   CT f[P2], nb[P2];
 #pragma unroll
   for (int q = 0; q < P2; ++q) f[q] = (CT)(ST)fe[q * nst];
@@ -201,8 +195,8 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
   for (int q = 0; q < P2; ++q) acc[q] = (CT)0;
 
   // x and y: lines inside the plane, lane-local (FP32 arithmetic on the matrix
-  // cores, see line_mfma: a block of four lanes is one velocity's planes for
-  // p >= 2, two velocities for p = 1). The neighbours' planes are loaded one
+  // cores, see line_mfma: a block of four lanes is one velocity's planes). The
+  // neighbours' planes are loaded one
   // axis at a time, behind a scheduling barrier.
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -274,33 +268,27 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int q = 0; q < P2; ++q) nb[q] = (CT)(ST)src[2][q * nst];
-  // z: the column of node q is spread over the group's lanes; lane lp holds
+  // z: the column of node q is spread over the quad's lanes; lane lp holds
   // plane lp and its partners lane ^ r the other planes. The derivative is
   // sum_r D[lp][lp ^ r] f(lp ^ r); the trace difference ext - own is one
-  // group sum of lext(lp) f_nb - lown(lp) f (zero weights on idle lanes).
+  // quad sum of lext(lp) f_nb - lown(lp) f.
   {
     const CT a = (CT)(vel.u[2] * g.scale[2]);
     const CT* ro = fr.r[pos[2] ? 1 : 0];
     const CT* re = fr.r[use_right[2] ? 0 : 1];
-    const CT lown_mine = live ? ro[pl] : (CT)0;
-    const CT lext_mine = live ? re[pl] : (CT)0;
-    const CT ag = a * ro[kMaxN1 + pl];
+    const CT lown_mine = ro[lp], lext_mine = re[lp];
+    const CT ag = a * ro[kMaxN1 + lp];
     CT Dr[G];
 #pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const int b = lp ^ r;
-      Dr[r] = live && b < N1 ? fr.D[pl * kMaxN1 + b] : (CT)0;
-    }
+    for (int r = 0; r < G; ++r) Dr[r] = fr.D[lp * kMaxN1 + (lp ^ r)];
 #pragma unroll
     for (int q = 0; q < P2; ++q) {
       const CT fq = f[q];
       CT df = Dr[0] * fq;
       df += Dr[1] * quad_xor<1>(fq);
-      if constexpr (G == 4) {
-        df += Dr[2] * quad_xor<2>(fq);
-        df += Dr[3] * quad_xor<3>(fq);
-      }
-      const CT jl = group_allsum<G>(lext_mine * nb[q] - lown_mine * fq);
+      df += Dr[2] * quad_xor<2>(fq);
+      df += Dr[3] * quad_xor<3>(fq);
+      const CT jl = quad_allsum(lext_mine * nb[q] - lown_mine * fq);
       acc[q] += a * df + ag * jl;
     }
   }
@@ -309,9 +297,9 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
   // the canonical layout
   const int cx = vel.b[0] - rp.x0, oy = rp.nx + vel.b[1] - rp.y0,
             oz = rp.nxy + vel.b[2] - rp.z0;
-  const double* tp = tab + pl * P2 * rp.ncols;  // rows of this lane's plane
+  const double* tp = tab + lp * P2 * rp.ncols;  // rows of this lane's plane
   const int jc = vel.b[0] + g.nv1[0] * (vel.b[1] + g.nv1[1] * vel.b[2]);
-  double* oe1 = (double*)A.out + ((e - A.out_e0) * NS + pl * P2) * nv + jc;
+  double* oe1 = (double*)A.out + ((e - A.out_e0) * NS + lp * P2) * nv + jc;
   const bool whole = whole_sectors(g);  // (a wave stores 16 velocities of a node)
   if (A.collide) {  // uniform: rows beyond the first batch, then the relaxation
     table_rest<kU>(tab, et, rp, tid);
@@ -331,19 +319,19 @@ __device__ __forceinline__ void residual3_item(const StageArgs& A, const int chu
 
 // Three waves per SIMD in FP64, four in FP32 arithmetic (the neighbours'
 // planes loaded one axis at a time).
-template <int P, typename ST, bool CAN>
+template <typename ST, bool CAN>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(sizeof(ST) == 8 ? 3 : 4))) k_residual3(const StageArgs A) {
   const int64_t w = xcd_chunk_remap(blockIdx.x, gridDim.x, A.ecount, A.xcd_part);
-  residual3_item<P, ST, CAN>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount), w == 0);
+  residual3_item<ST, CAN>(A, (int)(w / A.ecount), work_element(A.order, A.e0, w, A.ecount), w == 0);
 }
 
-template <int P, typename ST, bool CAN>
+template <typename ST, bool CAN>
 __global__ void __launch_bounds__(kBlock) k_moments3(const StageArgs A) {
   using CT = typename Compute<ST>::T;
   using Src = Source<CAN, ST>;
-  using PL = Plane3<P>;
-  constexpr int N1 = PL::N1, G = PL::G, VB = PL::VB, P2 = PL::P2, NS = PL::NS;
+  using PL = Plane3;
+  constexpr int G = PL::G, VB = PL::VB, P2 = PL::P2, NS = PL::NS;
   __shared__ double red[(kBlock / 64) * NS * 5];
   extern __shared__ __align__(16) unsigned char dyn_lds[];  // MFMA staging
   const DevGeom& g = A.g;
@@ -352,19 +340,17 @@ __global__ void __launch_bounds__(kBlock) k_moments3(const StageArgs A) {
   const int64_t e = work_element(A.order, A.e0, w, A.ecount);
   const int64_t nv = g.nv;
   const int lp = (int)threadIdx.x % G;
-  const bool live = lp < N1;
-  const int pl = live ? lp : N1 - 1;
   const int j = chunk * VB + (int)threadIdx.x / G;
   const bool valid = j < nv;
   const int jj = valid ? j : (int)nv - 1;
   Vel vel = velocity_of(g, jj);
-  if (!(valid && live)) vel.w = 0.0;
-  const typename Src::T* fe = (const typename Src::T*)A.fin + Src::offset(g, e, pl * P2, jj);
+  if (!valid) vel.w = 0.0;
+  const typename Src::T* fe = (const typename Src::T*)A.fin + Src::offset(g, e, lp * P2, jj);
   const int64_t nst = Src::stride(g);
   CT f[P2];
 #pragma unroll
   for (int q = 0; q < P2; ++q) f[q] = (CT)(ST)fe[q * nst];
-  plane_partials_mfma<P, ST, CT>(f, vel, A.partials, e * NS, g.nx, chunk, lp, dyn_lds, red,
+  plane_partials_mfma<ST, CT>(f, vel, A.partials, e * NS, g.nx, chunk, lp, dyn_lds, red,
                                  (int)threadIdx.x);
 }
 

@@ -734,13 +734,13 @@ static hipError_t hex_dispatch(int mode, bool inc, const StageArgs& A, size_t ta
   if constexpr (P == 3) {  // plane-split: FP64 storage, BF16 increments
     if (mode == 0) return launch_walk(sizeof(ST) == 8 ? 0 : 2, A, s);
     if (mode == 1) {
-      hipLaunchKernelGGL((k_residual3<P, ST, false>), grid, block, tab, s, A);
+      hipLaunchKernelGGL((k_residual3<ST, false>), grid, block, tab, s, A);
     } else if (mode == 3) {
-      hipLaunchKernelGGL((k_residual3<P, ST, true>), grid, block, tab, s, A);
+      hipLaunchKernelGGL((k_residual3<ST, true>), grid, block, tab, s, A);
     } else {
-      const size_t lds3 = std::max(tab, (size_t)mfma3_lds_bytes<P, ST>());
-      if (mode == 2) hipLaunchKernelGGL((k_moments3<P, ST, false>), grid, block, lds3, s, A);
-      else hipLaunchKernelGGL((k_moments3<P, ST, true>), grid, block, lds3, s, A);
+      const size_t lds3 = std::max(tab, (size_t)mfma3_lds_bytes<ST>());
+      if (mode == 2) hipLaunchKernelGGL((k_moments3<ST, false>), grid, block, lds3, s, A);
+      else hipLaunchKernelGGL((k_moments3<ST, true>), grid, block, lds3, s, A);
     }
     return hipGetLastError();
   }
@@ -897,7 +897,7 @@ bool hex_one_lane(int order, int precision) {
 
 int velocities_per_block(int dim, int order, int precision) {
   if (dim < 3 || hex_one_lane(order, precision)) return kBlock;
-  return order + 1 <= 2 ? Plane3<1>::VB : Plane3<3>::VB;
+  return Plane3::VB;
 }
 
 hipError_t launch_stage(int precision, int mode, const StageArgs& A, hipStream_t s) {

@@ -38,7 +38,8 @@ template <int DIM, int P, typename ST, int MODE, bool INC, int E>
 __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, const int ey,
                                          const int ex0, const int cnt, const bool count) {
   static_assert(DIM <= 2, "segments and quadrilaterals");
-  static_assert(!INC || (MODE != 1 && sizeof(ST) == 4), "increment stages: FP32 state, RK modes");
+  static_assert(MODE == 0 || MODE == 3, "RK stages");
+  static_assert(!INC || sizeof(ST) == 4, "increment stages: FP32 state");
   using CT = typename Compute<ST>::T;
   constexpr int N1 = P + 1;
   constexpr int NS = ipow(N1, DIM);
@@ -276,11 +277,6 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
   // is loaded; C in FP64, added in FP64
   const int cx = vel.b[0] - rp.x0, oy = rp.nx + vel.b[1] - rp.y0,
             oz = rp.nxy + vel.b[2] - rp.z0;
-  double* oe1 = nullptr;  // residual output (canonical layout, MODE 1)
-  if constexpr (MODE == 1) {
-    const int jc = vel.b[0] + g.nv1[0] * (vel.b[1] + g.nv1[1] * vel.b[2]);
-    oe1 = (double*)A.out + (e0 - A.out_e0) * NS * nv + jc;
-  }
   const CT dt = (CT)A.dt, ca = (CT)A.a, cb = (CT)A.b;
   const double wc = A.b * A.dt;
   if (A.collide) {
@@ -291,9 +287,7 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
       // (rows past the run's end: any row of the table)
       const int row = q / NS < cnt ? q : 0;
       const double c = collision_term(tab + row * rp.ncols, cx, oy, oz, rp.ncols, (double)f[q]);
-      if constexpr (MODE == 1) {
-        if (valid && q / NS < cnt) oe1[(int64_t)q * nv] = c - (double)acc[q];
-      } else if constexpr (sizeof(CT) == 8) {
+      if constexpr (sizeof(CT) == 8) {
         acc[q] = fma(wc, c, cb * (f[q] - dt * acc[q]));
       } else {
         acc[q] = (CT)fma(wc, c, (double)(cb * (f[q] - dt * acc[q])));
@@ -301,105 +295,95 @@ __device__ __forceinline__ void row_item(const StageArgs& A, const int chunk, co
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      if constexpr (MODE == 1) {
-        if (valid && q / NS < cnt) oe1[(int64_t)q * nv] = -(double)acc[q];
-      } else {
-        acc[q] = cb * (f[q] - dt * acc[q]);
-      }
+    for (int q = 0; q < R; ++q) acc[q] = cb * (f[q] - dt * acc[q]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  CT o[R], fnv[R];
+  if constexpr (INC) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) fnv[q] = fb[q];
+  } else if constexpr (MODE == 0) {
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const ST* fn = (const ST*)A.fn + own + (i < cnt ? i : cnt - 1) * estride;
+#pragma unroll
+      for (int q = 0; q < NS; ++q) fnv[i * NS + q] = (CT)__builtin_nontemporal_load(&fn[q * kVB]);
     }
   }
-  if constexpr (MODE == 1) {
-    if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
-  } else {
-    __builtin_amdgcn_sched_barrier(0);
-    CT o[R], fnv[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) o[q] = MODE == 0 ? ca * fnv[q] + acc[q] : acc[q];
+  if (A.limiter) {
+    int hits = 0, bad = 0;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      CT(&oi)[NS] = *reinterpret_cast<CT(*)[NS]>(&o[i * NS]);
+      CT fmin = oi[0];
+#pragma unroll
+      for (int q = 0; q < NS; ++q) fmin = oi[q] < fmin ? oi[q] : fmin;
+      const CT mean = tensor_wsum<DIM, N1>(oi, OP.w) / OP.Wsum;
+      const bool hit = valid && i < cnt && (fmin < (CT)0);
+      if (hit && mean != fmin) {
+        CT beta = fabs(mean / (mean - fmin));
+        beta = beta > (CT)1 ? (CT)1 : beta;
+#pragma unroll
+        for (int q = 0; q < NS; ++q) oi[q] = mean + beta * (oi[q] - mean);
+      }
+      hits += __popcll(__ballot(hit));
+      bad += __popcll(__ballot(hit && !(mean > (CT)0)));
+    }
+    limiter_count(lim, hits, bad, tid);
+  }
+  if (INC && !A.out_full) {
     if constexpr (INC) {
 #pragma unroll
-      for (int q = 0; q < R; ++q) fnv[q] = fb[q];
-    } else if constexpr (MODE == 0) {
-#pragma unroll
       for (int i = 0; i < E; ++i) {
-        const ST* fn = (const ST*)A.fn + own + (i < cnt ? i : cnt - 1) * estride;
+        const int64_t ooff = own + i * estride;
+        const bool live = valid && i < cnt;
+        uint32_t* ow = inc_pairs((uint16_t*)A.out, ooff);
+        float omin = INFINITY, smin = INFINITY;  // stage values / stored values
+        uint32_t wd[NS / 2];
 #pragma unroll
-        for (int q = 0; q < NS; ++q) fnv[i * NS + q] = (CT)__builtin_nontemporal_load(&fn[q * kVB]);
+        for (int q = 0; q + 1 < NS; q += 2) {
+          CT &o0 = o[i * NS + q], &o1 = o[i * NS + q + 1];
+          float s0, s1;
+          wd[q >> 1] = bf16_increment2(o0, o1, fnv[i * NS + q], fnv[i * NS + q + 1], s0, s1);
+          omin = fminf(omin, fminf(o0, o1));
+          smin = fminf(smin, fminf(s0, s1));
+          o0 = s0;
+          o1 = s1;
+        }
+        if constexpr (NS % 2 != 0) {  // odd last node
+          CT& ol = o[i * NS + NS - 1];
+          float stored;
+          const uint16_t h = bf16_increment(ol, fnv[i * NS + NS - 1], stored);
+          if (live) __builtin_nontemporal_store(h, (uint16_t*)A.out + ooff + (NS - 1) * kVB);
+          omin = fminf(omin, ol);
+          smin = fminf(smin, stored);
+          ol = stored;
+        }
+        if (live) {
+#pragma unroll
+          for (int m = 0; m < NS / 2; ++m) __builtin_nontemporal_store(wd[m], &ow[m * kVB]);
+        }
+        const unsigned long long nviol = __popcll(__ballot(live && smin < 0.0f && !(omin < 0.0f)));
+        if ((tid & 63) == 0 && nviol) atomicAdd(&A.diag[5], nviol);
       }
     }
+  } else if (valid) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) o[q] = MODE == 0 ? ca * fnv[q] + acc[q] : acc[q];
-    if (A.limiter) {
-      int hits = 0, bad = 0;
+    for (int i = 0; i < E; ++i) {
+      if (i < cnt) {
+        ST* oe = (ST*)A.out + own + i * estride;
 #pragma unroll
-      for (int i = 0; i < E; ++i) {
-        CT(&oi)[NS] = *reinterpret_cast<CT(*)[NS]>(&o[i * NS]);
-        CT fmin = oi[0];
-#pragma unroll
-        for (int q = 0; q < NS; ++q) fmin = oi[q] < fmin ? oi[q] : fmin;
-        const CT mean = tensor_wsum<DIM, N1>(oi, OP.w) / OP.Wsum;
-        const bool hit = valid && i < cnt && (fmin < (CT)0);
-        if (hit && mean != fmin) {
-          CT beta = fabs(mean / (mean - fmin));
-          beta = beta > (CT)1 ? (CT)1 : beta;
-#pragma unroll
-          for (int q = 0; q < NS; ++q) oi[q] = mean + beta * (oi[q] - mean);
-        }
-        hits += __popcll(__ballot(hit));
-        bad += __popcll(__ballot(hit && !(mean > (CT)0)));
-      }
-      limiter_count(lim, hits, bad, tid);
-    }
-    if (INC && !A.out_full) {
-      if constexpr (INC) {
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-          const int64_t ooff = own + i * estride;
-          const bool live = valid && i < cnt;
-          uint32_t* ow = inc_pairs((uint16_t*)A.out, ooff);
-          float omin = INFINITY, smin = INFINITY;  // stage values / stored values
-          uint32_t wd[NS / 2];
-#pragma unroll
-          for (int q = 0; q + 1 < NS; q += 2) {
-            CT &o0 = o[i * NS + q], &o1 = o[i * NS + q + 1];
-            float s0, s1;
-            wd[q >> 1] = bf16_increment2(o0, o1, fnv[i * NS + q], fnv[i * NS + q + 1], s0, s1);
-            omin = fminf(omin, fminf(o0, o1));
-            smin = fminf(smin, fminf(s0, s1));
-            o0 = s0;
-            o1 = s1;
-          }
-          if constexpr (NS % 2 != 0) {  // odd last node
-            CT& ol = o[i * NS + NS - 1];
-            float stored;
-            const uint16_t h = bf16_increment(ol, fnv[i * NS + NS - 1], stored);
-            if (live) __builtin_nontemporal_store(h, (uint16_t*)A.out + ooff + (NS - 1) * kVB);
-            omin = fminf(omin, ol);
-            smin = fminf(smin, stored);
-            ol = stored;
-          }
-          if (live) {
-#pragma unroll
-            for (int m = 0; m < NS / 2; ++m) __builtin_nontemporal_store(wd[m], &ow[m * kVB]);
-          }
-          const unsigned long long nviol = __popcll(__ballot(live && smin < 0.0f && !(omin < 0.0f)));
-          if ((tid & 63) == 0 && nviol) atomicAdd(&A.diag[5], nviol);
-        }
-      }
-    } else if (valid) {
-#pragma unroll
-      for (int i = 0; i < E; ++i) {
-        if (i < cnt) {
-          ST* oe = (ST*)A.out + own + i * estride;
-#pragma unroll
-          for (int q = 0; q < NS; ++q) __builtin_nontemporal_store((ST)o[i * NS + q], &oe[q * kVB]);
-        }
+        for (int q = 0; q < NS; ++q) __builtin_nontemporal_store((ST)o[i * NS + q], &oe[q * kVB]);
       }
     }
-    if (A.collide) lds_barrier();
-    element_partials_mfma<R, ST, CT>(o, vel, A.partials, node0, g.nx, chunk, dyn_lds, red, tid,
-                                     cnt * NS);
-    if (A.limiter) limiter_add(lim, A.diag, tid);  // (behind the partials' barrier)
-    if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
   }
+  if (A.collide) lds_barrier();
+  element_partials_mfma<R, ST, CT>(o, vel, A.partials, node0, g.nx, chunk, dyn_lds, red, tid,
+                                   cnt * NS);
+  if (A.limiter) limiter_add(lim, A.diag, tid);  // (behind the partials' barrier)
+  if (tid == 0 && count) atomicAdd(&A.diag[4], 1ull);
 }
 
 // Work items of a mesh: runs of E elements per row, velocity-chunk major.
