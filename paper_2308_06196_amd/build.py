@@ -19,8 +19,8 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libbgk.so")
 OBJDIR = os.path.join(ROOT, "_build")
-SOURCES = ["bgk_runtime.hip", "bgk_kernels.hip", "bgk_hexwalk.hip", "bgk_rows.hip",
-           "bgk_xwalk.hip"]
+SOURCES = ["bgk_runtime.hip", "bgk_kernels.hip", "bgk_exchange.hip", "bgk_hexwalk.hip",
+           "bgk_rows.hip", "bgk_xwalk.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=on",

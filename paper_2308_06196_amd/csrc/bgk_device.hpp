@@ -1486,7 +1486,9 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 // Residual L(f) of a canonical FP64 array (see Source). Bound by memory: one read
-// of f, one write of L. The output is stored non-temporally, as nothing reads it
+// of f, one write of L; every instantiation holds its element in registers (at most
+// 4 spilled, p = 3 quadrilaterals in FP32), which p = 3 hexahedra in FP32 would not
+// (356), so they are not built. The output is stored non-temporally, as nothing reads it
 // again here and the y neighbours' nodes then stay in the caches (residual calls,
 // us, plain / non-temporal: 27 x 31 p = 3 elements on 20^3 velocities 673 / 640, 10 x
 // 8 x 8 p = 2 elements on 16^3 527 / 487, 300 p = 2 line elements on 16^3 45.2 / 43.8).

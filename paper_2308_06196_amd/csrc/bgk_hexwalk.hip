@@ -100,10 +100,10 @@ static void small_mesh_tile(const DevGeom& g, int precision, int ncols, int mixe
 
 // Large meshes: rows of up to five elements: four kept two FP64 (three BF16)
 // work-groups per CU, where rows of eight leave one by their LDS (16^3-element
-// Taylor-Green box, ms per launch, rows of 2, 4, 8: FP64 5.30, 5.07, 6.44; BF16
-// 3.59, 3.41, 3.83). A work-group's start (its operators, and the first loads,
+// Taylor-Green box, ms per launch, rows of 2, 4, 8: FP64 5.22, 5.07, 6.30; BF16
+// 3.56, 3.47, 3.84). A work-group's start (its operators, and the first loads,
 // which nothing covers) costs as much as about 3.5 elements (tiles of 4 x 8
-// instead of 4 x 16: FP64 5.38, BF16 3.56), so a tile takes as many rows as leave
+// instead of 4 x 16: FP64 5.29, BF16 3.52), so a tile takes as many rows as leave
 // enough work-groups for the device: the count minimises (1 + 3.5 / elements)
 // / eff, eff = R / ceil(R) for R = work-groups / resident work-groups.
 void walk_tile(const DevGeom& g, int precision, int ncols, int* tx_out, int* ty_out) {

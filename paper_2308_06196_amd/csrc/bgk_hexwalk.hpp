@@ -82,10 +82,10 @@ __device__ __forceinline__ T rows_allmin(T x) {
 // Measured on the 16^3-element Taylor-Green box with 16^3 velocities (1.07e9
 // values), ms per stage launch averaged over a step, against the per-element
 // kernel this replaces (planes of one velocity in adjacent lanes, all three
-// neighbours' nodes read, five dependent load batches): FP64 5.07 against 9.77
+// neighbours' nodes read, five dependent load batches): FP64 5.06 against 9.77
 // (4.5 TB/s of compulsory traffic; stages 2-3 move 33.5 GB, the z-neighbours
-// that miss L2 among them, at 6.4 TB/s: bound by HBM); BF16 increments 3.41
-// against 5.27 (18.2 GB in stages 2-3 at 5 TB/s; vector issue 40 % busy).
+// that miss L2 among them, at 6.4 TB/s: bound by HBM); BF16 increments 3.47-3.65
+// by box against 5.27 (19.6 and 22.8 GB in stages 2 and 3; vector issue 40 % busy).
 // Waves per SIMD: two in FP64 (237 registers; three spill and take 10.6 ms),
 // three with increments (two 3.64 ms, four 5.06 ms).
 struct HexWalk {

@@ -49,7 +49,8 @@ struct XWalk {
   }
 };
 
-// Waves per SIMD: what the registers of a variant allow without spills.
+// Waves per SIMD: what the registers of a variant allow with at most one spilled
+// vector register (p = 1 hexahedra with increments).
 template <int DIM, int P, typename ST, bool INC>
 constexpr int xwalk_waves() {
   return DIM == 3 && P == 2 ? 2 : sizeof(ST) == 8 || (DIM == 2 && INC) ? 3 : 4;
