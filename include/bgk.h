@@ -220,7 +220,12 @@ bgk_status bgk_get_state(bgk_solver* s, double* f, int32_t where);
  * state is not modified. Device buffers: asynchronous on the stream.
  * Host buffers are staged through the workspace element by element
  * range; with FP32 storage this needs at least two elements
- * (BGK_ERR_UNSUPPORTED otherwise). */
+ * (BGK_ERR_UNSUPPORTED otherwise).
+ * A device f_in that r_out does not overlap is read in place, in its own
+ * velocity order; host buffers, overlapping device buffers and FP32 storage of
+ * order-3 hexahedra go through a copy in the internal order. The moments are
+ * then summed in another order, so the two ways differ in the last bits; each is
+ * deterministic. */
 bgk_status bgk_residual(bgk_solver* s, const double* f_in, double* r_out, int32_t where);
 
 /* Advance the installed state by nsteps steps of size dt with the
@@ -264,7 +269,8 @@ bgk_status bgk_collision_moments(bgk_solver* s, double* Cm, int32_t where);
  * of BGK_NOALLOC_SCRATCH_BYTES bytes. Calls no hipMalloc, hipFree or memset:
  * kernels only, queued on hip_stream (a hipStream_t or NULL), asynchronous;
  * the counters are cleared by a kernel at the start of every call. The
- * result equals bgk_residual's for the same problem and input.
+ * result equals bgk_residual's for the same problem and the same device
+ * buffers.
  * Errors: BGK_ERR_INVALID_ARG / BGK_ERR_UNSUPPORTED as bgk_query_footprint;
  * BGK_ERR_UNSUPPORTED for diffuse walls; BGK_ERR_OUT_OF_MEMORY (nothing
  * queued) when the problem needs more scratch than the array holds (about

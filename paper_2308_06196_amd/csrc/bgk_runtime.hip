@@ -581,9 +581,9 @@ void brick_order(const int32_t* ne, std::vector<int32_t>& out) {
 // Whether the residual of a canonical device array is formed in place: not for
 // p = 3 hexahedra in FP32, whose 64 nodes of one lane then have addresses of
 // their own (nodes are nv values apart, a run-time stride): 356 spilled
-// registers, and the call took 8.07 ms on 10 x 8 x 8 elements with 16^3
+// registers, and the call took 8.40 ms on 10 x 8 x 8 elements with 16^3
 // velocities where the copy to the internal layout, whose node offsets are
-// immediates, takes 1.40 (16^3 elements 51.3 / 9.04 ms, 3^3 on 8^3 186 / 48 us). The
+// immediates, takes 1.07 (16^3 elements 53.5 / 6.81 ms). The
 // other kernels gain from it (FP32 p = 2 hexahedra 581 / 457 us on 10 x 8 x 8).
 bool reads_canonical(const bgk_solver* s) {
   return !(s->pb.dim == 3 && s->pb.order == 3 && s->precision == BGK_FP32);
